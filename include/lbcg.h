@@ -280,7 +280,11 @@ const char *lbcg_strerror(int status);
 
 /* Launch shape chosen for the handle: kernel kind (LBCG_KERNEL_GENERIC,
  * LBCG_KERNEL_FUSED or LBCG_KERNEL_COMPACT), rows per block, z chunks, tile
- * width (64; or 32 on the compact D3Q19 sweep).  rows 0 on the fused kernel:
+ * width (64; or 32 on the compact D3Q19 sweep).  A periodic D3Q19 lattice
+ * whose launch shape is automatic may be stepped by a pair of kernels with one
+ * thread per node instead of the sweep, bitwise the same, where that is faster
+ * (lattices that fill the device only in part); the sweep's shape that it
+ * stands for is reported.  rows 0 on the fused kernel:
  * the split step of a D3Q19 lattice with geometry (one kernel pulls and
  * writes every fluid node's psi and collision moments, a second forms the
  * gradient, collides and stores, a third stores inlet and outlet values;
@@ -292,7 +296,7 @@ int lbcg_launch_info(lbcg_sim *s, int32_t *kernel, int32_t *rows, int32_t *zchun
 /* Choose the fused (or compact) kernel's launch shape for this handle by
  * timing candidate shapes on the handle's own lattice (D3Q19: rows 4 or 8,
  * 8 only for the compact kernel, which also tries 32-wide tiles, and with a
- * geometry mask the split step; z splits
+ * geometry mask the split step, without one the two-kernel step; z splits
  * that fill the device once, twice or four times and chunks of 2 to 64
  * planes; D2Q9: row chunks of 8 to 512 rows), stepping the current state
  * into the spare buffer so the state does not change (the compact kernel is

@@ -72,6 +72,9 @@ struct FusedShape {
     int rows;     // rows of the x-y tile (one wave of 64 nodes per row)
     int zchunks;  // z range split per column of tiles
     int tx = 64;  // tile width (the compact D3Q19 sweep: 64 or 32)
+    // periodic D3Q19 lattices: the split step of lbcg_split.hip instead of
+    // the sweep (rows, zchunks and tx then only say which sweep it replaces)
+    bool split = false;
 };
 
 // Kernel view of one lattice for the fused sweep.
@@ -137,6 +140,15 @@ hipError_t launch_expand_cgeo(int prec, const Geo &g, const void *cin, void *pou
 hipError_t launch_step_split(int prec, const Geo &g, const ModelD &md, const void *in, void *out, void *psi,
                              void *scratch, const SplitPlan &sp, const uint32_t *ctr_in, uint32_t *ctr_out,
                              hipStream_t s);
+
+// Split step of periodic D3Q19 lattices (F32 or F16 storage, regularized):
+// a moments kernel and a collision kernel, bitwise the sweeps' results.
+// compact_in / compact_out: the state read / written is compact (else
+// pairs); psi: pitch floats; mom (compact_out only; a pair step keeps its
+// moments in `out`): kSplitMoments * pitch floats.
+hipError_t launch_step_psplit(int prec, const Geo &g, const ModelD &md, const void *in, bool compact_in, void *out,
+                              bool compact_out, void *psi, void *mom, const uint32_t *ctr_in, uint32_t *ctr_out,
+                              hipStream_t s);
 
 // Fused single-pass D2Q9 step on periodic lattices, F32 or F16 storage:
 // strips of 64 columns, each row range split into ychunks.

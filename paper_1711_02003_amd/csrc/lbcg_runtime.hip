@@ -153,6 +153,9 @@ bool any_fused_supported(int lattice, int prec, const Geo &g) {
 
 hipError_t launch_fused(const lbcg_sim *s, const void *in, void *out, const uint32_t *ctr_in, uint32_t *ctr_out,
                         FusedShape shape) {
+    if (shape.split)
+        return launch_step_psplit(s->prec, s->g, s->md, in, false, out, false, s->psi, nullptr, ctr_in, ctr_out,
+                                  s->stream);
     if (shape.rows == 0)
         return launch_step_split(s->prec, s->g, s->md, in, out, s->psi, s->moms, s->split, ctr_in, ctr_out,
                                  s->stream);
@@ -167,7 +170,64 @@ hipError_t launch_compact(const lbcg_sim *s, const void *in, bool pair_in, void 
                           uint32_t *ctr_out, FusedShape shape) {
     if (s->lattice == LBCG_D2Q9)
         return launch_step_compact2d(s->g, s->md, in, pair_in, out, ctr_in, ctr_out, shape.zchunks, s->stream);
+    // the moments go to the pair buffer that holds no state (a compact
+    // handle's pair buffers hold the state of its first step and what reads
+    // of the state expand, both in buf[cur])
+    if (shape.split)
+        return launch_step_psplit(s->prec, s->g, s->md, in, !pair_in, out, true, s->psi, s->buf[s->cur ^ 1], ctr_in,
+                                  ctr_out, s->stream);
     return launch_step_compact(s->prec, s->g, s->md, in, pair_in, out, ctr_in, ctr_out, shape, s->stream);
+}
+
+// Blocks of the D3Q19 sweep of shape sh that the device holds at once.
+int64_t resident_blocks(const lbcg_sim *s, const FusedShape &sh) {
+    return s->kernel == LBCG_KERNEL_COMPACT
+               ? compact_resident_blocks(sh.tx, s->prec)
+               : fused_resident_blocks(s->prec, sh.rows, s->g.mask != nullptr, s->collision != LBCG_REGULARIZED);
+}
+
+// Plane iterations that the D3Q19 sweep takes one after another with zc z
+// chunks: the blocks run in rounds of `resident`, and each pulls its own
+// planes and about three more (the planes before and after, and the start).
+int64_t sweep_planes(const lbcg_sim *s, const FusedShape &sh, int64_t resident, int64_t zc) {
+    const int64_t tiles = int64_t((s->g.nx + sh.tx - 1) / sh.tx) * ((s->g.ny + sh.rows - 1) / sh.rows);
+    return (tiles * zc + resident - 1) / resident * ((s->g.nz + zc - 1) / zc + 3);
+}
+
+// The z split of a sweep with the fewest plane iterations in a row.  (As few
+// chunks as fill the device once, the rule before, left a second round of
+// blocks half empty: 210 x 150 x 131 FP32 548 us per step with 4 chunks, 304
+// blocks on 256 CUs, against 398 with 3, and short columns of planes unsplit:
+// 45 x 38 x 53 62 us with 6 chunks, 20 with 27.)
+int64_t best_zchunks(const lbcg_sim *s, const FusedShape &sh, int64_t resident) {
+    int64_t best = 1, cost = 0;
+    for (int64_t zc = 1; zc <= s->g.nz && zc <= 4096; ++zc) {
+        const int64_t c = sweep_planes(s, sh, resident, zc);
+        if (zc == 1 || c < cost) {
+            cost = c;
+            best = zc;
+        }
+    }
+    return best;
+}
+
+bool split_allowed(const lbcg_sim *s) {
+    return s->lattice == LBCG_D3Q19 && !s->g.mask && s->collision == LBCG_REGULARIZED &&
+           (s->kernel == LBCG_KERNEL_FUSED || s->kernel == LBCG_KERNEL_COMPACT);
+}
+
+// Whether the split step of a periodic D3Q19 lattice is expected to be faster
+// than the sweep of shape sh: the sweep's plane iterations at the time one
+// takes with every CU busy (256^3: 131 of them), against the split step's
+// time per node plus its two launches.  Per state and storage, measured:
+// plane 8.6 / 5.7 / 6.5 / 5.2 us (pair FP32, compact FP32, pair FP16, compact
+// FP16), node 80 / 70 / 54 / 55 ps.
+bool split_faster(const lbcg_sim *s, const FusedShape &sh) {
+    const bool cmp = s->kernel == LBCG_KERNEL_COMPACT, half = s->prec == LBCG_F16;
+    const double plane_us = half ? (cmp ? 5.2 : 6.5) : (cmp ? 5.7 : 8.6);
+    const double node_us = half ? (cmp ? 55e-6 : 54e-6) : (cmp ? 70e-6 : 80e-6);
+    const double sweep = double(sweep_planes(s, sh, resident_blocks(s, sh), sh.zchunks)) * plane_us;
+    return 8.0 + double(s->g.N) * node_us < sweep;
 }
 
 FusedShape pick_shape(const lbcg_sim *s, const lbcg_params *p) {
@@ -209,18 +269,10 @@ FusedShape pick_shape(const lbcg_sim *s, const lbcg_params *p) {
     sh.tx = p->tile[2] ? p->tile[2] : 64;
     int zc = p->tile[1];
     if (!zc && (s->kernel == LBCG_KERNEL_FUSED || s->kernel == LBCG_KERNEL_COMPACT)) {
-        // One wave of resident blocks: each z chunk re-reads two planes, so use
-        // as few (long) chunks as fill the device, but keep chunks >= 8 planes.
-        const int64_t tiles = int64_t((s->g.nx + sh.tx - 1) / sh.tx) * ((s->g.ny + sh.rows - 1) / sh.rows);
-        const int64_t resident = s->kernel == LBCG_KERNEL_COMPACT
-                                     ? compact_resident_blocks(sh.tx, s->prec)
-                                     : fused_resident_blocks(s->prec, sh.rows, s->g.mask != nullptr,
-                                                             s->collision != LBCG_REGULARIZED);
-        int64_t want = (resident + tiles - 1) / tiles;
-        const int64_t cap = s->g.nz / 8 > 1 ? s->g.nz / 8 : 1;
-        zc = int(want < 1 ? 1 : (want > cap ? cap : want));
+        zc = int(best_zchunks(s, sh, resident_blocks(s, sh)));
     }
     sh.zchunks = zc < 1 ? 1 : zc;
+    sh.split = split_allowed(s) && !p->tile[0] && !p->tile[1] && !p->tile[2] && split_faster(s, sh);
     return sh;
 }
 
@@ -809,7 +861,7 @@ int lbcg_tune(lbcg_sim *s, int32_t *rows, int32_t *zchunks) {
             if (s->collision != LBCG_REGULARIZED && r != 8) continue;  // plain BGK: 8-row tiles
             const int64_t resident = cmp ? compact_resident_blocks(tx, s->prec)
                                          : fused_resident_blocks(s->prec, r, masked, s->collision != LBCG_REGULARIZED);
-            std::vector<int64_t> zs = {1};
+            std::vector<int64_t> zs = {1, best_zchunks(s, FusedShape{r, 1, tx}, resident)};
             for (int m : {1, 2, 4}) zs.push_back((m * resident + tiles - 1) / tiles);
             for (int planes : {2, 4, 8, 16, 32, 64}) zs.push_back((s->g.nz + planes - 1) / planes);
             for (int64_t z : zs) {
@@ -818,6 +870,14 @@ int lbcg_tune(lbcg_sim *s, int32_t *rows, int32_t *zchunks) {
                 for (const FusedShape &c : cand) seen = seen || (c.rows == r && c.zchunks == zc && c.tx == tx);
                 if (!seen) cand.push_back(FusedShape{r, zc, tx});
             }
+        }
+        // periodic D3Q19: the split step, reported with the sweep shape that
+        // it replaces
+        if (split_allowed(s) && !cand.empty()) {
+            FusedShape c{8, 1, 64};
+            c.zchunks = int(best_zchunks(s, c, resident_blocks(s, c)));
+            c.split = true;
+            cand.push_back(c);
         }
         // The compact kernel is timed as every later step runs it: reading a
         // compact state.  Before the handle's first compact step (the state is
@@ -880,7 +940,8 @@ int lbcg_tune(lbcg_sim *s, int32_t *rows, int32_t *zchunks) {
         (void)hipEventDestroy(e0);
         (void)hipEventDestroy(e1);
         if (e != hipSuccess) return dev_err(e);
-        if (pick.rows != s->shape.rows || pick.zchunks != s->shape.zchunks || pick.tx != s->shape.tx) {
+        if (pick.rows != s->shape.rows || pick.zchunks != s->shape.zchunks || pick.tx != s->shape.tx ||
+            pick.split != s->shape.split) {
             for (int k = 0; k < 2; ++k)
                 if (s->graph[k]) {
                     (void)hipGraphExecDestroy(s->graph[k]);
