@@ -25,7 +25,7 @@ of every node (both colours).  Prints one JSON line:
              pair_f32 (the same lattice on the pair-state sweep: per
              population its total and minority share), f16 (the same lattice
              with FP16 storage, compact and pair state), d2q9 (a 4096^2 D2Q9 box: compact and
-             pair-state strip sweeps and the two-pass generic kernel),
+             pair-state tile steps and the two-pass generic kernel),
              focusing2d (the 8192 x 2048 D2Q9 junction), focusing (the
              512 x 128 x 64 D3Q19 flow-focusing junction, FP32 and FP16),
              batched, batched_compact and batched_compact_f16 (64 uneven
@@ -230,9 +230,9 @@ def f16_form(torch, lbcg, W, size, steps=200, warmup=10):
 
 
 def d2q9_form(torch, lbcg, W, steps=200, warmup=10):
-    """D2Q9 4096^2 with 256 droplets, FP32 storage: the fused strip sweep on
-    the compact state (tuned; 104 B per node: every total and the senders'
-    4 colour scalars read and written once), on the pair state (tuned; 144 B
+    """D2Q9 4096^2 with 256 droplets, FP32 storage: the fused tile step on
+    the compact state (104 B per node: every total and the senders'
+    4 colour scalars read and written once), on the pair state (144 B
     per node: one read and one write of every population pair) and, for
     comparison, the two-pass generic kernel (a psi pass, then the step)
     against the same 144 B."""
@@ -243,40 +243,30 @@ def d2q9_form(torch, lbcg, W, steps=200, warmup=10):
         stream = torch.cuda.Stream()
         sim = lbcg.Sim.from_workload(w, precision="f32", kernel=kernel, stream=stream.cuda_stream)
         sim.step(2)
-        if kernel != lbcg.KERNEL_GENERIC:
-            sim.tune()
         ms = time_sim(torch, sim, stream, steps, warmup)
-        info = sim.launch_info()
         sim.close()
         gbs = bpn * w.fluid_nodes * steps / (ms / 1e3) / 1e9
         out[name] = {"mlups": round(w.fluid_nodes * steps / (ms / 1e3) / 1e6, 1),
                      "ms_per_step": round(ms / steps, 4), "achieved_gbs": round(gbs, 1),
                      "frac": round(gbs / HBM_PEAK_GBS, 4), "bytes_per_node": bpn}
-        if kernel != lbcg.KERNEL_GENERIC:
-            out[name]["ychunks"] = info["zchunks"]
     return out
 
 
 def focusing2d_form(torch, lbcg, W, steps=200, warmup=10):
     """D2Q9 flow-focusing junction 8192 x 2048 (the paper's 2-D device
-    geometry: walls, three inlets, an outlet), FP32: the fused strip sweep
-    (tuned) and the two-pass generic kernel, fluid-node MLUPS."""
+    geometry: walls, three inlets, an outlet), FP32: the fused tile step
+    and the two-pass generic kernel, fluid-node MLUPS."""
     w = W.flow_focusing_2d(8192, 2048)
     out = {"workload": w.name, "fluid_nodes": w.fluid_nodes, "nodes": w.nodes, "steps": steps}
     for name, kernel in (("fused", lbcg.KERNEL_FUSED), ("generic", lbcg.KERNEL_GENERIC)):
         stream = torch.cuda.Stream()
         sim = lbcg.Sim.from_workload(w, precision="f32", kernel=kernel, stream=stream.cuda_stream)
         sim.step(1)
-        if kernel == lbcg.KERNEL_FUSED:
-            sim.tune()
         ms = time_sim(torch, sim, stream, steps, warmup)
-        info = sim.launch_info()
         sim.close()
         out[name] = {"mlups": round(w.fluid_nodes * steps / (ms / 1e3) / 1e6, 1),
                      "ms_per_step": round(ms / steps, 4),
                      "frac": round((144 + 4) * w.fluid_nodes * steps / (ms / 1e3) / 1e9 / HBM_PEAK_GBS, 4)}
-        if kernel == lbcg.KERNEL_FUSED:
-            out[name]["ychunks"] = info["zchunks"]
     return out
 
 

@@ -60,7 +60,7 @@ extern "C" {
  * rate 1/tau_k (the literal baseline of Fig. 1; it does not keep momentum
  * where tau_R != tau_B).  Both BGK forms run on the generic kernel and,
  * with F32 or F16 storage, on the fused sweeps: the D3Q19 column sweep
- * (tiles of 8 rows, tile[0] 0 or 8) and the D2Q9 strip sweep; not on the
+ * (tiles of 8 rows, tile[0] 0 or 8) and the D2Q9 tile step; not on the
  * split step of D3Q19 lattices with geometry, the compact state or the
  * batched sweeps. */
 #define LBCG_REGULARIZED 0
@@ -167,7 +167,8 @@ typedef struct {
     int32_t n_walls;     /* entries in walls (<= 64) */
     const lbcg_wall *walls;     /* host, copied */
     int32_t tile[3];     /* fused-kernel launch shape: rows per block (4 or 8;
-                            D3Q19 only), z chunks (D2Q9: row chunks; <= 4096),
+                            D3Q19 only), z chunks (<= 4096; D2Q9, whose step
+                            has one shape, only reports the number given),
                             tile width (64; the compact D3Q19 sweep also 32:
                             256-thread blocks, several per compute unit);
                             0 = automatic.  With a geometry mask on D3Q19,
@@ -298,11 +299,11 @@ int lbcg_launch_info(lbcg_sim *s, int32_t *kernel, int32_t *rows, int32_t *zchun
  * 8 only for the compact kernel, which also tries 32-wide tiles, and with a
  * geometry mask the split step, without one the two-kernel step; z splits
  * that fill the device once, twice or four times and chunks of 2 to 64
- * planes; D2Q9: row chunks of 8 to 512 rows), stepping the current state
+ * planes), stepping the current state
  * into the spare buffer so the state does not change (the compact kernel is
  * timed on a compact state also before the handle's first compact step).  Keeps
  * the fastest shape for later steps and reports it.  No effect on the
- * generic kernel.  Synchronizes. */
+ * generic kernel and on D2Q9, whose step has one launch shape.  Synchronizes. */
 int lbcg_tune(lbcg_sim *s, int32_t *rows, int32_t *zchunks);
 
 /* Batched form (the paper's method applied to many independent lattices at

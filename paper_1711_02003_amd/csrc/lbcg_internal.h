@@ -150,11 +150,11 @@ hipError_t launch_step_psplit(int prec, const Geo &g, const ModelD &md, const vo
                               bool compact_out, void *psi, void *mom, const uint32_t *ctr_in, uint32_t *ctr_out,
                               hipStream_t s);
 
-// Fused single-pass D2Q9 step on periodic lattices, F32 or F16 storage:
-// strips of 64 columns, each row range split into ychunks.
-hipError_t launch_step_fused2d(int prec, const Geo &g, const ModelD &md, const void *in, void *out,
-                               const uint32_t *ctr_in, uint32_t *ctr_out, int ychunks, hipStream_t s);
-bool fused2d_supported(int prec, const Geo &g);
+// Fused single-pass D2Q9 step over tiles (lbcg_tile2d.hip): F64, F32 or F16
+// storage, with or without geometry, any collision form.
+hipError_t launch_step_tile2d(int prec, const Geo &g, const ModelD &md, const void *in, void *out,
+                              const uint32_t *ctr_in, uint32_t *ctr_out, hipStream_t s);
+bool tile2d_supported(int prec, const Geo &g);
 
 // Fused D3Q19 step on the compact state (periodic, regularized, tiles of 8
 // rows, FP32 or FP16 storage): 19 arrays of pitch totals and 5 colour
@@ -171,11 +171,11 @@ bool compact_supported(int lattice, int prec, const Geo &g);
 int compact_resident_blocks(int tile_width, int prec);
 // Pair state (post-collision, as the pair kernels store it) of a compact state.
 hipError_t launch_expand(int prec, const Geo &g, const void *cin, void *pout, hipStream_t s);
-// The D2Q9 strip sweep on the compact state (periodic, FP32, regularized):
-// 9 arrays of pitch floats and 4 colour scalars per node in one record
-// array, kCompactBytes2d per pitch node; rows split into ychunks.
+// The D2Q9 step on the compact state (periodic, FP32, regularized): 9 arrays
+// of pitch floats and 4 colour scalars per node in one record array,
+// kCompactBytes2d per pitch node.
 hipError_t launch_step_compact2d(const Geo &g, const ModelD &md, const void *in, bool pair_in, void *out,
-                                 const uint32_t *ctr_in, uint32_t *ctr_out, int ychunks, hipStream_t s);
+                                 const uint32_t *ctr_in, uint32_t *ctr_out, hipStream_t s);
 hipError_t launch_expand2d(const Geo &g, const void *cin, void *pout, hipStream_t s);
 
 // Batched fused step: one launch steps many lattices by one time level.

@@ -191,9 +191,9 @@ def traffic_summary(fetch_csv, write_csv, kernel_sub, timed, nodes, out_txt, com
 FORM_KERNELS = [("D3Q19 256³ droplets, FP32 pairs", r"k_step_fused<float, float, \d, false, false>"),
                 ("D3Q19 256³ droplets, FP16 compact", r"k_step_compactILb0ELi\d+EDF16_"),
                 ("D3Q19 256³ droplets, FP16 pairs", r"k_step_fusedIDF16_fLi\dELb0ELb0E"),
-                ("D2Q9 4096² droplets, FP32 compact", r"k_step_compact2d<false>"),
-                ("D2Q9 4096² droplets, FP32", r"k_step_fused2d<float, false>"),
-                ("D2Q9 junction 8192×2048, FP32", r"k_step_fused2d<float, true>"),
+                ("D2Q9 4096² droplets, FP32 compact", r"k_tile2d_compact<"),
+                ("D2Q9 4096² droplets, FP32", r"k_tile2d<float, float, false, false, false"),
+                ("D2Q9 junction 8192×2048, FP32", r"k_tile2d<float, float, true, false, false"),
                 ("D3Q19 junction 512×128×64, FP32 split: moments", r"k_geo_moments<float>"),
                 ("D3Q19 junction 512×128×64, FP32 split: collision", r"k_geo_collide<float>"),
                 ("D3Q19 junction 512×128×64, FP32 split: inlets, outlets", r"k_geo_boundary<float>"),
