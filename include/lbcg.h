@@ -78,7 +78,7 @@ extern "C" {
  * storage; with a geometry mask D3Q19 with F32 or F16 storage on the split
  * step of the fused kernel (launch shape fixed, tile all 0; a link from a
  * wall brings back the node's own population, a link from an inlet or an
- * outlet reads the pair that the boundary kernel stores in the pair
+ * outlet reads the pair that the step before stored in the pair
  * buffer); the pair state (2Q x 4 x pitch bytes for F32, 2Q x 2 x pitch for
  * F16) below 4 GiB (pitch = node count rounded up to 64).  Eq. (10) splits
  * every population of a node with coefficients that depend only on that
@@ -202,8 +202,8 @@ typedef struct lbcg_sim lbcg_sim;
 /* Device bytes lbcg_create needs for these parameters (two state buffers, the
  * phase-field scratch, the mask and link words, reduction scratch, a field
  * staging area, the two compact buffers of the compact kernel and, for a
- * D3Q19 F32 or F16 lattice with geometry, the split step's scratch: 12
- * collision moments and a node-list entry per node, and per-block lists).
+ * D3Q19 F32 or F16 lattice with geometry, the split step's scratch of 52
+ * bytes per node, of which it uses the psi and node-list entries).
  * Used for admission by footprint. */
 int lbcg_footprint(const lbcg_params *p, size_t *bytes);
 
@@ -288,9 +288,9 @@ const char *lbcg_strerror(int status);
  * stands for is reported.  rows 0 on the fused kernel:
  * the split step of a D3Q19 lattice with geometry (one kernel pulls and
  * writes every fluid node's psi and collision moments, a second forms the
- * gradient, collides and stores, a third stores inlet and outlet values;
- * bitwise the column sweep's results, without the sweep's recomputed tile
- * ring and chunk halo, which dominate where the fluid fills few tiles).
+ * gradient, collides and stores, inlet and outlet values included; bitwise
+ * the column sweep's results, without the sweep's recomputed tile ring and
+ * chunk halo, which dominate where the fluid fills few tiles).
  * NULL outputs are skipped. */
 int lbcg_launch_info(lbcg_sim *s, int32_t *kernel, int32_t *rows, int32_t *zchunks, int32_t *tile_width);
 
@@ -317,9 +317,11 @@ int lbcg_tune(lbcg_sim *s, int32_t *rows, int32_t *zchunks);
  * tile: {rows per block (4 or 8; 8 on the compact kernel), z planes per
  * chunk (>= 1)}; NULL or {0, 0}
  * = choose by timing candidate shapes on the batch (the states do not
- * change).  Errors: LBCG_E_INVAL for a violated requirement, LBCG_E_NOMEM /
- * LBCG_E_DEVICE for allocation or HIP failures.  The batch allocates its
- * own small descriptor tables (device and pinned host memory).
+ * change), among them, for up to 256 handles, the split steps in place of the
+ * sweep of the periodic and of the geometry lattices.  Errors: LBCG_E_INVAL
+ * for a violated requirement, LBCG_E_NOMEM / LBCG_E_DEVICE for allocation or
+ * HIP failures.  The batch allocates its own small descriptor tables (device
+ * and pinned host memory).
  *
  * lbcg_batch_step advances lattice j by nsteps[j] >= 0 steps (n entries),
  * asynchronously on the shared stream.  Results per lattice are bitwise those
@@ -342,10 +344,12 @@ void lbcg_batch_destroy(lbcg_batch *b);
  * nsteps[j] >= 0 steps (n entries) with the launch shape tile = {rows per
  * block (4 or 8; 8 on the compact kernel), z planes per chunk (>= 1)}; the
  * requirements on the handles are those of lbcg_batch_create, and all must
- * belong to the device current at the call.  Results per lattice are bitwise
- * those of lbcg_batch_step and lbcg_step.
+ * belong to the device current at the call.  Periodic or geometry lattices
+ * step on the split steps instead where that is expected to be faster (narrow
+ * or mostly solid lattices).  Results per lattice are bitwise those of
+ * lbcg_batch_step and lbcg_step.
  * The descriptors and block tables live in one fixed area of device memory
- * that the library holds per device until the process ends (about 1.1 MB),
+ * that the library holds per device until the process ends (about 1.2 MB),
  * written by small kernels queued on the handles' stream: at most
  * LBCG_NOALLOC_MAX_LATTICES lattices per call and LBCG_NOALLOC_MAX_BLOCKS
  * blocks per level for each of the periodic and the geometry groups; larger

@@ -618,32 +618,38 @@ struct OwnMom {
     T rho, rR, u[3];
 };
 template <class L, typename S, typename T>
-__device__ __forceinline__ OwnMom<T> own_moments(const typename PairOf<S>::type *enc) {
-    T drho = 0, Ra = 0, Ba = 0, jx = 0, jy = 0, jz = 0;
+struct OwnSum {
+    T drho = 0, Ra = 0, jx = 0, jy = 0, jz = 0;
     int K = 0;
-#pragma unroll
-    for (int k = 0; k < L::Q; ++k) {
+    __device__ __forceinline__ void add(int k, typename PairOf<S>::type v) {
         bool fl;
-        const T d = Codec<S>::template df<L, T>(enc[k].x, k);
-        const T m = Codec<S>::template col<T>(enc[k].y, fl);
+        const T d = Codec<S>::template df<L, T>(v.x, k);
+        const T m = Codec<S>::template col<T>(v.y, fl);
         const T mu = m * (T(w36<L>(k)) + T(36) * d);
         const T t = T(36) * d - mu;
         drho += d;
         Ra += fl ? t : mu;
-        Ba += fl ? mu : t;
         K += fl ? w36<L>(k) : 0;
         jx += T(L::cx[k]) * d;
         jy += T(L::cy[k]) * d;
         jz += T(L::cz[k]) * d;
     }
-    OwnMom<T> om;
-    om.rho = T(1) + drho;
-    om.rR = (T(K) + Ra) / T(36);
-    om.u[0] = jx / om.rho;
-    om.u[1] = jy / om.rho;
-    om.u[2] = jz / om.rho;
-    (void)Ba;
-    return om;
+    __device__ __forceinline__ OwnMom<T> moments() const {
+        OwnMom<T> om;
+        om.rho = T(1) + drho;
+        om.rR = (T(K) + Ra) / T(36);
+        om.u[0] = jx / om.rho;
+        om.u[1] = jy / om.rho;
+        om.u[2] = jz / om.rho;
+        return om;
+    }
+};
+template <class L, typename S, typename T>
+__device__ __forceinline__ OwnMom<T> own_moments(const typename PairOf<S>::type *enc) {
+    OwnSum<L, S, T> s;
+#pragma unroll
+    for (int k = 0; k < L::Q; ++k) s.add(k, enc[k]);
+    return s.moments();
 }
 
 // The scalars of an inlet (velocity and colour densities) or an outlet

@@ -10,411 +10,347 @@
 //     moments the collision needs (drho, 36 rho^R, 36 rho^B, j, trace-adjusted
 //     flux S: 12 values) and psi (Eq. (4) input), and writes them;
 //   k_geo_collide: each fluid node forms the colour gradient from its
-//     neighbours' psi (neutral walls and outlets: its own psi; inlets and
-//     wetting walls: their phase value), collides (Eqs. (9)-(11)) and
-//     stores its 19 new pairs and, for links from walls, their bounce-back
-//     values;
-//   k_geo_boundary: each fluid node with links from inlets or outlets
-//     stores their values (from its new pairs, read back); one thread per
-//     such node and direction, from a list of the nodes.
+//     neighbours' psi, collides (Eqs. (9)-(11)) and stores its 19 new pairs
+//     and, for links from non-fluid nodes, their boundary values.
 // Every value is computed by the expressions and in the order of the column
 // sweep, so the results are bitwise those of the sweep.  Traffic per fluid
 // node: pairs read and written once (2 x 38 x E bytes), plus 12 moments and
-// psi written and read once (2 x 52 bytes), the neighbours' psi from cache,
-// and at nodes next to a boundary their new pairs read back.  The same three
-// kernels also run on the compact state (below): 2 x 96 (FP32) or 2 x 50
-// (FP16) bytes of state per fluid node instead of 2 x 152 or 2 x 76.
-#include "lbcg_buffer.h"
-#include "lbcg_compact_sweep.h"  // CStore: the compact state's storage
-#include "lbcg_internal.h"
+// psi written and read once (2 x 52 bytes) and the neighbours' psi from cache.
+// The same kernels also run on the compact state (below): 2 x 96 (FP32) or 2 x
+// 50 (FP16) bytes of state per fluid node instead of 2 x 152 or 2 x 76.
+//
+// Work: thread k takes entry k of the list of fluid nodes {node, link word},
+// built once per lattice in node order.  Blocks of 64 x 4 nodes (with a list
+// of those that hold fluid) left a third of the lanes idle on step-emulsifier
+// channels and read the link words of solid nodes: 412 us a level for eight
+// of them (FP32) against 370.  With the nodes that have inlet or outlet links
+// first in the list, in waves of their own, the collision of the 512 x 128 x
+// 64 junction took 54 us instead of 64, but such a wave on a face across x
+// touches 64 lines per access: its moments took 47 instead of 43, and a 256 x
+// 64 x 32 junction 52 us a step instead of 33 (16-bit, compact).
+//
+// psi: non-fluid nodes hold what they show the gradient, written once when
+// the lattice is made (the inlet's or wetting wall's phase value, or kPsiOwn
+// where the fluid node's own psi stands in), so the gradient is 19 plain
+// loads; looking each non-fluid neighbour up in the mask took the collision
+// kernel 110 registers and 1560 vector instructions.
+//
+// The moments lie in the fluid node's own slots of the buffer that the step
+// writes (see lbcg_split.hip): the lines come from the caches when the new
+// state is stored, and an area of their own is neither written nor read.  On
+// the 512 x 128 x 64 junction (FP32) 50 + 58 us against 62 + 70; on the
+// compact state, collision kernel only, 37 us (FP16: 30) against 40 (34).
+//
+// Inlet and outlet values.  On pairs the collision kernel forms them from each
+// new pair as it is stored, at 112 registers: 62 us on that junction against
+// 57 without them and 6 and a launch in a kernel of their own, and on eight
+// step-emulsifier channels 190 against 174 + 45.  On the compact state, where
+// the values go to another buffer, a kernel of one thread per link follows:
+// 37 + 6 us against 48 (FP16: 30 + 6 against 54).
+#include "lbcg_split.h"
 
 namespace lbcg {
 
 namespace {
 
-// Blocks of 64 x 4 nodes of one z plane (a wave per x row), numbered plane
-// first, then y range, then x range; the kernels run only the blocks in
-// their list (in that order).  Blocks go to the 8 XCDs round-robin, so
-// every XCD gets an even share of each tile's planes whatever the channel
-// layout.  Numbered x range first, a lattice 512 wide (8 x ranges) gives
-// each XCD one x range, and a channel that crosses the lattice in y then
-// runs on one XCD; numbered y range first, the junction's kernels measured
-// 1.5 to 1.8 x slower than plane first.  Launching every block of the
-// lattice, solid ones included, cost each kernel about 15 us on the
-// junction (16384 blocks, 70 % of them solid).
-constexpr int kGX = kSplitGX, kGY = kSplitGY, kGeoBlock = kGX * kGY;
-constexpr int kNM = kSplitMoments;  // moments per node
+constexpr int kGeoBlock = 256;
+constexpr int kIoBlock = 64;
+constexpr int kChunk = 1024;  // nodes per count of the list builder
 
-template <typename S>
-struct SplitArgs {
-    FusedArgs<S> a;
-    float *psi;                 // psi of every fluid node
-    float *mom;                 // kNM arrays of pitch floats
-    const uint32_t *blocks;     // the kernel's block list (the boundary kernel's: its node list)
-};
-
-// Scratch layout: the moments, then the per-block flags, the per-block
-// counts of nodes with inlet or outlet links, the list of blocks with fluid,
-// the list of blocks with inlet or outlet links, the offsets of their nodes
-// in the node list, the node list and the three lengths.
+// Scratch: psi of every node, the list of fluid nodes {node, link word}, that
+// of the ones with inlet or outlet links, the counts of the list builder (two
+// per chunk of nodes) and the totals.  (The lists have the room that the
+// moments' 48 bytes per node once took.)
 struct ScratchMap {
-    float *mom;
-    uint8_t *flags;
-    uint16_t *ioc;
-    uint32_t *act, *io, *ioofs, *ionodes, *counts;
+    float *psi;
+    uint32_t *list, *io;
+    uint32_t *counts, *totals;
 };
-__host__ __device__ inline size_t align256(size_t v) { return (v + 255) / 256 * 256; }
-inline ScratchMap scratch_map(void *scratch, int64_t pitch, int64_t nb) {
+inline size_t align256(size_t v) { return (v + 255) / 256 * 256; }
+inline ScratchMap scratch_map(void *scratch, int64_t pitch) {
     char *p = static_cast<char *>(scratch);
+    const size_t chunks = size_t((pitch + kChunk - 1) / kChunk);
     ScratchMap m;
-    m.mom = reinterpret_cast<float *>(p);
-    p += align256(sizeof(float) * kNM * size_t(pitch));
-    m.flags = reinterpret_cast<uint8_t *>(p);
-    p += align256(size_t(nb));
-    m.ioc = reinterpret_cast<uint16_t *>(p);
-    p += align256(sizeof(uint16_t) * size_t(nb));
-    m.act = reinterpret_cast<uint32_t *>(p);
-    p += align256(sizeof(uint32_t) * size_t(nb));
+    m.psi = reinterpret_cast<float *>(p);
+    p += align256(sizeof(float) * size_t(pitch));
+    m.list = reinterpret_cast<uint32_t *>(p);
+    p += align256(2 * sizeof(uint32_t) * size_t(pitch));
     m.io = reinterpret_cast<uint32_t *>(p);
-    p += align256(sizeof(uint32_t) * size_t(nb));
-    m.ioofs = reinterpret_cast<uint32_t *>(p);
-    p += align256(sizeof(uint32_t) * size_t(nb));
-    m.ionodes = reinterpret_cast<uint32_t *>(p);
-    p += align256(sizeof(uint32_t) * size_t(pitch));
+    p += align256(2 * sizeof(uint32_t) * size_t(pitch));
     m.counts = reinterpret_cast<uint32_t *>(p);
+    p += align256(2 * sizeof(uint32_t) * chunks);
+    m.totals = reinterpret_cast<uint32_t *>(p);
     return m;
 }
 
-// The node of this thread in block b (false outside the lattice), and the
-// node index x' + nx (y' + ny z') of its neighbour x + (dx, dy, dz)
-// (periodic).  Node indices fit 32 bits: the state buffers are below 4 GiB.
-struct Here {
-    int x, y, z;
-    uint32_t n;
-};
-__device__ __forceinline__ bool here(int nx, int ny, int nz, uint32_t b, Here &h) {
-    const uint32_t nby = uint32_t(uniform((ny + kGY - 1) / kGY)), nzu = uint32_t(uniform(nz));
-    const uint32_t t = b / nzu, u = t / nby;
-    h.z = int(b - t * nzu);
-    h.y = int(t - u * nby) * kGY + int(threadIdx.x / kGX);
-    h.x = int(u) * kGX + int(threadIdx.x % kGX);
-    h.n = uint32_t(h.x) + uint32_t(nx) * (uint32_t(h.y) + uint32_t(ny) * uint32_t(h.z));
-    return h.x < nx && h.y < ny;
-}
-__device__ __forceinline__ uint32_t nbr(int nx, int ny, int nz, const Here &h, int dx, int dy, int dz) {
-    const uint32_t xs = uint32_t(wrap_m1(h.x + dx, nx)), ys = uint32_t(wrap_m1(h.y + dy, ny)),
-                   zs = uint32_t(wrap_m1(h.z + dz, nz));
-    return xs + uint32_t(nx) * (ys + uint32_t(ny) * zs);
-}
-
-// A node whose link from a non-fluid neighbour is not a wall's: the
-// boundary kernel stores that link's value.
+// A fluid node with a link from a non-fluid node that is not a wall (mixed
+// codes count: each link is checked where it is used).
 __device__ __forceinline__ bool has_io_link(uint32_t lk) {
-    return (lk & kLinkFluid) && (lk & kLinkBits) && ((lk & kLinkMixed) || !is_wall(link_code(lk)));
+    return (lk & kLinkBits) && ((lk & kLinkMixed) || !is_wall(link_code(lk)));
 }
 
-// Rank of this thread's node among the block's nodes with `pred` (in
-// thread order) and, through `total`, their count.
-__device__ __forceinline__ uint32_t block_rank(bool pred, uint32_t &total) {
-    __shared__ uint32_t wc[kGeoBlock / 64];
-    const uint64_t bal = __builtin_amdgcn_ballot_w64(pred);
-    const uint32_t lane = __builtin_amdgcn_mbcnt_hi(uint32_t(bal >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(bal), 0u));
+// List builder.  Block b goes through nodes [b kChunk, (b + 1) kChunk):
+// without lists it counts its fluid nodes and those with inlet or outlet
+// links; with them it writes their entries from the offsets that k_geo_scan
+// put in place of the counts.
+__global__ void __launch_bounds__(kGeoBlock) k_geo_list(const uint32_t *__restrict__ links, uint32_t N,
+                                                       uint32_t *__restrict__ counts, uint32_t *__restrict__ list,
+                                                       uint32_t *__restrict__ io) {
+    __shared__ uint32_t wc[2][kGeoBlock / 64];
     const int w = int(threadIdx.x / 64);
-    if (threadIdx.x % 64 == 0) wc[w] = uint32_t(__builtin_popcountll(bal));
-    __syncthreads();
-    uint32_t before = 0, all = 0;
-    for (int k = 0; k < kGeoBlock / 64; ++k) {
-        before += k < w ? wc[k] : 0u;
-        all += wc[k];
-    }
-    total = all;
-    return before + lane;
-}
-
-// Flags of block b: 1 = some node fluid, 2 = some node with an inlet or
-// outlet link (mixed codes count: the boundary kernel checks each link);
-// and the number of such nodes.
-__global__ void __launch_bounds__(kGeoBlock) k_geo_flags(const uint32_t *__restrict__ links, int nx, int ny, int nz,
-                                                        uint8_t *__restrict__ flags, uint16_t *__restrict__ ioc) {
-    Here h;
-    const bool in = here(nx, ny, nz, blockIdx.x, h);
-    const uint32_t lk = in ? links[h.n] : 0u;
-    const int f = __syncthreads_or((lk & kLinkFluid) != 0u);
-    uint32_t nio = 0;
-    block_rank(has_io_link(lk), nio);
-    if (threadIdx.x == 0) {
-        flags[blockIdx.x] = uint8_t((f ? 1 : 0) | (nio ? 2 : 0));
-        ioc[blockIdx.x] = uint16_t(nio);
-    }
-}
-
-// The two block lists in ascending block order, and for each listed io
-// block the offset of its nodes in the io node list, by one block: thread t
-// takes the flags of a contiguous range, counts, and writes its entries
-// after the counts of the threads before it.
-constexpr int kListThreads = 1024;
-__global__ void __launch_bounds__(kListThreads) k_geo_lists(const uint8_t *__restrict__ flags,
-                                                           const uint16_t *__restrict__ ioc, uint32_t nb,
-                                                           uint32_t *__restrict__ act, uint32_t *__restrict__ io,
-                                                           uint32_t *__restrict__ ioofs,
-                                                           uint32_t *__restrict__ counts) {
-    __shared__ uint32_t ca[kListThreads], ci[kListThreads], cn[kListThreads], tot[3];
-    const uint32_t per = (nb + kListThreads - 1) / kListThreads;
-    const uint32_t b0 = min(nb, threadIdx.x * per), b1 = min(nb, b0 + per);
-    uint32_t na = 0, ni = 0, nn = 0;
-    for (uint32_t b = b0; b < b1; ++b) {
-        na += flags[b] & 1u;
-        ni += (flags[b] >> 1) & 1u;
-        nn += ioc[b];
-    }
-    ca[threadIdx.x] = na;
-    ci[threadIdx.x] = ni;
-    cn[threadIdx.x] = nn;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        uint32_t sa = 0, si = 0, sn = 0;
-        for (int t = 0; t < kListThreads; ++t) {
-            const uint32_t va = ca[t], vi = ci[t], vn = cn[t];
-            ca[t] = sa;
-            ci[t] = si;
-            cn[t] = sn;
-            sa += va;
-            si += vi;
-            sn += vn;
+    uint32_t at[2] = {0, 0};
+    if (list)
+        for (int c = 0; c < 2; ++c) at[c] = counts[2 * blockIdx.x + c];
+    for (uint32_t k = 0; k < kChunk; k += kGeoBlock) {
+        const uint32_t n = blockIdx.x * kChunk + k + threadIdx.x;
+        const uint32_t lk = n < N ? links[n] : 0u;
+        const bool mine[2] = {(lk & kLinkFluid) != 0u, (lk & kLinkFluid) && has_io_link(lk)};
+        uint32_t e[2];
+        __syncthreads();  // the counts of the pass before have been read
+        for (int c = 0; c < 2; ++c) {
+            const uint64_t bal = __builtin_amdgcn_ballot_w64(mine[c]);
+            e[c] = at[c] + __builtin_amdgcn_mbcnt_hi(uint32_t(bal >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(bal), 0u));
+            if (threadIdx.x % 64 == 0) wc[c][w] = uint32_t(__builtin_popcountll(bal));
         }
-        tot[0] = sa;
-        tot[1] = si;
-        tot[2] = sn;
+        __syncthreads();
+        for (int c = 0; c < 2; ++c) {
+            for (int v = 0; v < kGeoBlock / 64; ++v) {
+                e[c] += v < w ? wc[c][v] : 0u;
+                at[c] += wc[c][v];
+            }
+            uint32_t *to = c == 0 ? list : io;
+            if (list && mine[c]) {
+                to[2 * size_t(e[c])] = n;
+                to[2 * size_t(e[c]) + 1] = lk;
+            }
+        }
+    }
+    if (!list && threadIdx.x == 0)
+        for (int c = 0; c < 2; ++c) counts[2 * blockIdx.x + c] = at[c];
+}
+
+// Counts to offsets in the two lists, by one block: thread t takes a
+// contiguous range of chunks.
+constexpr int kScanThreads = 1024;
+__global__ void __launch_bounds__(kScanThreads) k_geo_scan(uint32_t *__restrict__ counts, uint32_t chunks,
+                                                          uint32_t *__restrict__ totals) {
+    __shared__ uint32_t s[2][kScanThreads];
+    const uint32_t per = (chunks + kScanThreads - 1) / kScanThreads;
+    const uint32_t b0 = min(chunks, threadIdx.x * per), b1 = min(chunks, b0 + per);
+    for (int c = 0; c < 2; ++c) {
+        uint32_t sum = 0;
+        for (uint32_t b = b0; b < b1; ++b) sum += counts[2 * b + c];
+        s[c][threadIdx.x] = sum;
     }
     __syncthreads();
-    if (threadIdx.x < 3) counts[threadIdx.x] = tot[threadIdx.x];  // a lane each: no wide store
-    uint32_t oa = ca[threadIdx.x], oi = ci[threadIdx.x], on = cn[threadIdx.x];
-    for (uint32_t b = b0; b < b1; ++b) {
-        if (flags[b] & 1u) act[oa++] = b;
-        if (flags[b] & 2u) {
-            ioofs[oi] = on;
-            io[oi++] = b;
-            on += ioc[b];
+    if (threadIdx.x < 2) {
+        uint32_t t = 0;
+        for (int k = 0; k < kScanThreads; ++k) {
+            const uint32_t v = s[threadIdx.x][k];
+            s[threadIdx.x][k] = t;
+            t += v;
+        }
+        totals[threadIdx.x] = t;
+    }
+    __syncthreads();
+    for (int c = 0; c < 2; ++c) {
+        uint32_t at = s[c][threadIdx.x];
+        for (uint32_t b = b0; b < b1; ++b) {
+            const uint32_t v = counts[2 * b + c];
+            counts[2 * b + c] = at;
+            at += v;
         }
     }
 }
 
-// The io node list: block k of the io block list writes its nodes with
-// inlet or outlet links, in thread order, from offset ioofs[k].
-__global__ void __launch_bounds__(kGeoBlock) k_geo_ionodes(const uint32_t *__restrict__ links, int nx, int ny, int nz,
-                                                          const uint32_t *__restrict__ io,
-                                                          const uint32_t *__restrict__ ioofs,
-                                                          uint32_t *__restrict__ ionodes) {
-    Here h;
-    const bool in = here(nx, ny, nz, io[blockIdx.x], h);
-    const bool mine = in && has_io_link(links[h.n]);
-    uint32_t total = 0;
-    const uint32_t r = block_rank(mine, total);
-    if (mine) ionodes[ioofs[blockIdx.x] + r] = h.n;
-}
-
-// psi that a non-fluid node shows the gradient of a fluid neighbour: the
-// inlet's or the wetting wall's phase value; neutral walls and outlets show
-// the fluid node's own psi (pc)
-template <typename S>
-__device__ __forceinline__ float solid_psi(const FusedArgs<S> &a, uint8_t c, float pc) {
+// What the non-fluid nodes show the gradient of a fluid neighbour.
+__global__ void __launch_bounds__(kGeoBlock) k_geo_solid_psi(Geo g, float *__restrict__ psi) {
+    const int64_t n = int64_t(blockIdx.x) * kGeoBlock + threadIdx.x;
+    if (n >= g.N) return;
+    const uint8_t c = g.mask[n];
+    if (c == kFluid) return;
+    float v = kPsiOwn;
     if (is_inlet(c)) {
-        const DevInlet in = a.inlets[c - kInlet0];
-        return float((in.rhoR - in.rhoB) / (in.rhoR + in.rhoB));
+        const DevInlet in = g.inlets[c - kInlet0];
+        v = float((in.rhoR - in.rhoB) / (in.rhoR + in.rhoB));
+    } else if (c >= kWall0 && c < kOutlet0) {
+        v = float(g.walls[c - kWall0].psi);
     }
-    if (c >= kWall0 && c < kOutlet0) return float(a.walls[c - kWall0].psi);
-    return pc;
+    psi[n] = v;
 }
 
-template <typename S>
-__global__ void __launch_bounds__(kGeoBlock) k_geo_moments(SplitArgs<S> sa) {
-    using L = D3Q19;
-    typedef float T;
-    typedef typename PairOf<S>::type P2;
-    constexpr uint32_t E = sizeof(P2);
-    const FusedArgs<S> &a = sa.a;
+// The fluid node of this thread in block `item` (false past the end), its
+// link word and its surroundings.
+typedef Around<false> Near;
+struct Here {
+    uint32_t n, lk, x, y, z;
+};
+__device__ __forceinline__ Here node_at(const SplitDesc &a, uint32_t n, uint32_t lk) {
     Here h;
-    if (!here(a.nx, a.ny, a.nz, sa.blocks[blockIdx.x], h)) return;
-    const uint32_t n = h.n;
-    if (!(a.links[n] & kLinkFluid)) return;
-    const uint32_t cstride = uint32_t(a.pitch) * E;
-    const __amdgpu_buffer_rsrc_t rin = state_rsrc(a.in, uint32_t(L::Q) * cstride);
-    P2 v[L::Q];
-#pragma unroll
-    for (int i = 0; i < L::Q; ++i) {
-        const uint32_t m = nbr(a.nx, a.ny, a.nz, h, -L::cx[i], -L::cy[i], -L::cz[i]);
-        v[i] = load_pair<P2>(rin, m * E, uint32_t(i) * cstride);
-    }
-    Pops<L, T> q;
-    q.red = 0;
-#pragma unroll
-    for (int i = 0; i < L::Q; ++i) decode_pair<L, S, T>(v[i], i, q);
-    Mom<T> mm;
-    moments<L, T>(q, mm);
-    sa.psi[n] = float(psi_of<T>(mm.drho, mm.r36R, mm.r36B));
-    const float vals[kNM] = {mm.drho, mm.r36R, mm.r36B, mm.j[0], mm.j[1], mm.j[2],
-                             mm.S[0], mm.S[1], mm.S[2], mm.S[3], mm.S[4], mm.S[5]};
-#pragma unroll
-    for (int k = 0; k < kNM; ++k) sa.mom[int64_t(k) * a.pitch + n] = vals[k];
+    h.n = n;
+    h.lk = lk;
+    const uint32_t row = div_by(n, a.div0);
+    h.z = div_by(row, a.div1);
+    h.y = row - h.z * a.div1.d;
+    h.x = n - row * a.div0.d;
+    return h;
 }
-
-// Collision kernel, the moments kernel's blocks, one plane per block (a
-// block stepping its tile column up a chunk of 4 or 8 planes with the next
-// plane's loads in flight measured slower on the junction: 104 and 147
-// against 92 us, with more registers and fewer blocks).
-template <typename S>
-__global__ void __launch_bounds__(kGeoBlock) k_geo_collide(SplitArgs<S> sa, Model<float> mo) {
-    using L = D3Q19;
-    typedef float T;
-    typedef typename PairOf<S>::type P2;
-    constexpr uint32_t E = sizeof(P2);
-    const FusedArgs<S> &a = sa.a;
-    if (blockIdx.x == 0 && threadIdx.x == 0) *a.ctr_out = *a.ctr_in + 1u;
-    if (!sa.blocks) return;  // no fluid node
-    Here h;
-    if (!here(a.nx, a.ny, a.nz, sa.blocks[blockIdx.x], h)) return;
-    const uint32_t n = h.n;
-    const uint32_t clk = a.links[n];
-    if (!(clk & kLinkFluid)) return;
-    const uint32_t step = *a.ctr_in;  // seeds the stochastic rounding of 16-bit shares
-
-    // colour gradient from the neighbours' psi, in the column sweep's order
-    const float pc = sa.psi[n];
-    T fx = 0, fy = 0, fz = 0;
-#pragma unroll
-    for (int i = 1; i < L::Q; ++i) {
-        const uint32_t m = nbr(a.nx, a.ny, a.nz, h, L::cx[i], L::cy[i], L::cz[i]);
-        // x + c_i is the upstream node of the opposite link
-        const float pv = ((clk >> L::opp[i]) & 1u) ? solid_psi(a, a.mask[m], pc) : sa.psi[m];
-        const T wp = T(3.0 * wgt<L>(i)) * T(pv);
-        if (L::cx[i]) fx += L::cx[i] > 0 ? wp : -wp;
-        if (L::cy[i]) fy += L::cy[i] > 0 ? wp : -wp;
-        if (L::cz[i]) fz += L::cz[i] > 0 ? wp : -wp;
-    }
-    const T F[3] = {fx, fy, fz};
-    T mv[kNM];
-#pragma unroll
-    for (int k = 0; k < kNM; ++k) mv[k] = sa.mom[int64_t(k) * a.pitch + n];
-    const T cj[3] = {mv[3], mv[4], mv[5]}, cS[6] = {mv[6], mv[7], mv[8], mv[9], mv[10], mv[11]};
-    PostOut<L, T> o;
-    collide<L, T>(mo, mv[0], mv[1], mv[2], cj, cS, F, nullptr, o);
-    Dither dz(step, n);
-    const uint32_t cstride = uint32_t(a.pitch) * E;
-    const __amdgpu_buffer_rsrc_t rout = state_rsrc(a.out, uint32_t(L::Q) * cstride);
-    // Each new pair is stored as soon as it is encoded; where the link of the
-    // opposite direction comes from a wall, the same pair is also its
-    // half-way bounce-back value, stored in the wall node's slot.
-#pragma unroll
-    for (int j = 0; j < L::Q; ++j) {
-        const P2 v = encode_step<L, S, T>(o.df[j], o.mm[j], (o.red >> j) & 1u, j, dz);
-        store_pair<P2>(rout, n * E, uint32_t(j) * cstride, v);
-        const int i = L::opp[j];
-        if (j != 0 && ((clk >> i) & 1u)) {
-            const uint32_t m = nbr(a.nx, a.ny, a.nz, h, -L::cx[i], -L::cy[i], -L::cz[i]);
-            if (is_wall((clk & kLinkMixed) ? a.mask[m] : link_code(clk)))
-                store_pair<P2>(rout, m * E, uint32_t(i) * cstride, v);
-        }
-    }
-}
-
-// Inlet and outlet values: every fluid node with a link from an inlet or an
-// outlet reads back the new pairs it stored and writes, for each such link,
-// the value it will pull through it at the next step into the upstream
-// node's slot (the rules of the column sweep, from the same stored pairs).
-// Kept out of the collision kernel, whose registers they would take from 59
-// to 137.  A wave takes one direction i (uniform over the wave) for 64 nodes
-// of the io node list; lanes whose node has no inlet or outlet link i leave
-// at once.  One thread per node looping over its 18 links took 12-13 us on
-// the 512 x 128 x 64 junction (7 936 such nodes, one wave per CU, each wave
-// running the 18 links' code one after another); one thread per block node
-// over the io blocks, 13 us.
-constexpr int kIoBlock = 64;
-
-// Opposite of D3Q19 direction i from the numbering (rest; +x -x +y -y +z -z;
-// then per plane (+,+) (+,-) (-,+) (-,-)), for a direction known only at run
-// time; checked against the lattice table at compile time.
-__host__ __device__ constexpr int opp19(int i) {
-    return i == 0 ? 0 : i <= 6 ? ((i & 1) ? i + 1 : i - 1) : i - 2 * ((i - 7) % 4) + 3;
-}
-constexpr bool opp19_matches() {
-    for (int i = 0; i < D3Q19::Q; ++i)
-        if (opp19(i) != D3Q19::opp[i]) return false;
+__device__ __forceinline__ bool here(const SplitDesc &a, uint32_t item, Here &h) {
+    const uint32_t k = item * kGeoBlock + threadIdx.x;
+    if (k >= a.count) return false;
+    const uint2 e = reinterpret_cast<const uint2 *>(a.list)[k];
+    h = node_at(a, e.x, e.y);
     return true;
 }
-static_assert(opp19_matches(), "D3Q19 opposite directions");
-
-// Link I of node n; so_i and so_o are the byte offsets of the arrays of
-// directions I and opp(I), passed in from before any branch that lanes take
-// differently, so that they stay in scalar registers.
-template <int I, typename S>
-__device__ __forceinline__ void io_link(const FusedArgs<S> &a, const Model<float> &mo, uint32_t n, uint32_t so_i,
-                                        uint32_t so_o) {
-    using L = D3Q19;
-    typedef float T;
-    typedef typename PairOf<S>::type P2;
-    constexpr uint32_t E = sizeof(P2);
-    const uint32_t clk = a.links[n];
-    if (!((clk >> I) & 1u)) return;
-    Here h;
-    const uint32_t t = n / uint32_t(a.nx);
-    h.n = n;
-    h.x = int(n - t * uint32_t(a.nx));
-    h.z = int(t / uint32_t(a.ny));
-    h.y = int(t - uint32_t(h.z) * uint32_t(a.ny));
-    const uint32_t m = nbr(a.nx, a.ny, a.nz, h, -L::cx[I], -L::cy[I], -L::cz[I]);
-    const uint8_t c = (clk & kLinkMixed) ? a.mask[m] : link_code(clk);
-    if (is_wall(c)) return;
-    const uint32_t cstride = uint32_t(a.pitch) * E;
-    const __amdgpu_buffer_rsrc_t rout = state_rsrc(a.out, uint32_t(L::Q) * cstride);
-    Geo g{};
-    g.inlets = a.inlets;
-    g.outlets = a.outlets;
-    OwnMom<T> om{};
-    P2 own;
-    if (c >= kOutlet0) {
-        // outlet values need the node's own moments, from all its new pairs
-        P2 ov[L::Q];
-#pragma unroll
-        for (int i = 0; i < L::Q; ++i) ov[i] = load_pair<P2>(rout, n * E, uint32_t(i) * cstride);
-        om = own_moments<L, S, T>(ov);
-        own = ov[L::opp[I]];
-    } else {
-        own = load_pair<P2>(rout, n * E, uint32_t(uniform(int(so_o))));
-    }
-    store_pair<P2>(rout, m * E, uint32_t(uniform(int(so_i))),
-                   boundary_pair_v<L, S, T>(mo, I, c, io_vals<T>(g, c), own, om));
+__device__ __forceinline__ Near near(const SplitDesc &a, const Here &h) {
+    return Near(h.x, h.y, h.z, uint32_t(a.nx), uint32_t(a.ny), uint32_t(a.nz));
 }
 
+// The moments' slots: those of FP32 pairs are 8 bytes wide, those of FP16
+// pairs and of the FP32 compact state's totals 4, of the FP16 totals 2.
+template <typename S, bool COMPACT>
+using GeoMom = std::conditional_t<COMPACT && sizeof(S) == 2, MomHalves, MomStore<sizeof(S) == 4 && !COMPACT>>;
+
+template <typename S, bool COMPACT>
+__device__ __forceinline__ void geo_put(const SplitDesc &a, const Here &h, const Mom<float> &m) {
+    put_psi(a.psi, a.pitch, h.n, 0u, float(psi_of<float>(m.drho, m.r36R, m.r36B)));
+    GeoMom<S, COMPACT>::put(a.mom, a.pitch, h.n, 0u, m);
+}
+
+template <typename S, bool COMPACT>
+__device__ __forceinline__ void geo_moments(const SplitDesc &a, uint32_t item) {
+    Here h;
+    if (!here(a, item, h)) return;
+    Pops<D3Q19, float> q;
+    pull_pairs<S>(a.in, a.pitch, near(a, h), q);
+    Mom<float> m;
+    moments<D3Q19, float>(q, m);
+    geo_put<S, COMPACT>(a, h, m);
+}
+
+// The wall links among a fluid node's non-fluid links.
+__device__ __forceinline__ uint32_t wall_links(const SplitDesc &a, uint32_t lk, const Near &ar) {
+    using L = D3Q19;
+    if (!(lk & kLinkMixed)) return is_wall(link_code(lk)) ? lk & kLinkBits : 0u;
+    uint32_t wall = 0;
+#pragma unroll
+    for (int i = 1; i < L::Q; ++i)
+        if ((lk >> i) & 1u) wall |= is_wall(a.mask[ar.vo(i)]) ? (1u << i) : 0u;
+    return wall;
+}
+
+// Inlet and outlet links of a wave's nodes: the value that a node will pull
+// through such a link at the next step, from its new pair of the opposite
+// direction as stored and, for outlets, the moments of its stored pairs.
+// Waves without such nodes skip it, the others run the directions that their
+// nodes have (a face: five).
 template <typename S>
-__global__ void __launch_bounds__(kIoBlock) k_geo_boundary(SplitArgs<S> sa, Model<float> mo, uint32_t count) {
-    // block b: direction 1 + b % 18 of list entries 64 (b / 18) .. + 63
+struct IoLinks {
     typedef typename PairOf<S>::type P2;
-    const uint32_t b = blockIdx.x, chunk = b / 18u, dir = 1u + (b - chunk * 18u);
-    const uint32_t cstride = uint32_t(sa.a.pitch) * uint32_t(sizeof(P2));
-    const uint32_t so_i = dir * cstride, so_o = uint32_t(opp19(int(dir))) * cstride;
-    const uint32_t k = chunk * kIoBlock + threadIdx.x;
-    if (k >= count) return;
-    const uint32_t n = sa.blocks[k];
-    switch (dir) {
-        case 1: io_link<1, S>(sa.a, mo, n, so_i, so_o); break;
-        case 2: io_link<2, S>(sa.a, mo, n, so_i, so_o); break;
-        case 3: io_link<3, S>(sa.a, mo, n, so_i, so_o); break;
-        case 4: io_link<4, S>(sa.a, mo, n, so_i, so_o); break;
-        case 5: io_link<5, S>(sa.a, mo, n, so_i, so_o); break;
-        case 6: io_link<6, S>(sa.a, mo, n, so_i, so_o); break;
-        case 7: io_link<7, S>(sa.a, mo, n, so_i, so_o); break;
-        case 8: io_link<8, S>(sa.a, mo, n, so_i, so_o); break;
-        case 9: io_link<9, S>(sa.a, mo, n, so_i, so_o); break;
-        case 10: io_link<10, S>(sa.a, mo, n, so_i, so_o); break;
-        case 11: io_link<11, S>(sa.a, mo, n, so_i, so_o); break;
-        case 12: io_link<12, S>(sa.a, mo, n, so_i, so_o); break;
-        case 13: io_link<13, S>(sa.a, mo, n, so_i, so_o); break;
-        case 14: io_link<14, S>(sa.a, mo, n, so_i, so_o); break;
-        case 15: io_link<15, S>(sa.a, mo, n, so_i, so_o); break;
-        case 16: io_link<16, S>(sa.a, mo, n, so_i, so_o); break;
-        case 17: io_link<17, S>(sa.a, mo, n, so_i, so_o); break;
-        default: io_link<18, S>(sa.a, mo, n, so_i, so_o); break;
+    uint32_t io, any;  // the lane's links, the wave's
+    IoVals<float> iv;
+    OwnMom<float> om;
+    __device__ __forceinline__ IoLinks(const SplitDesc &a, const Here &h, uint32_t wall) : io(0), any(0), iv{}, om{} {
+        io = h.lk & kLinkBits & ~wall;
+        if (__builtin_amdgcn_ballot_w64(io != 0u) == 0) return;
+#pragma unroll
+        for (int i = 1; i < D3Q19::Q; ++i)
+            if (__builtin_amdgcn_ballot_w64((io >> i) & 1u) != 0) any |= 1u << i;
+        if (io && !(h.lk & kLinkMixed)) iv = vals(a, link_code(h.lk));
     }
+    __device__ __forceinline__ bool outlets(const Here &h) const {
+        return any && __builtin_amdgcn_ballot_w64((h.lk & kLinkOutlet) != 0u) != 0;
+    }
+    __device__ __forceinline__ static IoVals<float> vals(const SplitDesc &a, uint8_t c) {
+        Geo g{};
+        g.inlets = a.inlets;
+        g.outlets = a.outlets;
+        return io_vals<float>(g, c);
+    }
+    // link i, from the node's new pair `own` of direction opp(i)
+    __device__ __forceinline__ void put(const SplitDesc &a, const Here &h, const Near &ar, __amdgpu_buffer_rsrc_t rg,
+                                        int i, P2 own) {
+        constexpr uint32_t E = sizeof(P2);
+        if (!((any >> i) & 1u)) return;  // uniform over the wave
+        if (!((io >> i) & 1u)) return;
+        uint8_t c = link_code(h.lk);
+        if (h.lk & kLinkMixed) {
+            c = a.mask[ar.vo(i)];
+            iv = vals(a, c);
+        }
+        store_pair<P2>(rg, ar.vo(i) * E, uint32_t(su(uint32_t(i) * a.pitch * E)),
+                       boundary_pair_v<D3Q19, S, float>(a.mo, i, c, iv, own, om));
+    }
+};
+
+template <typename S>
+__device__ __forceinline__ void geo_collide(const SplitDesc &a, uint32_t item) {
+    using L = D3Q19;
+    typedef typename PairOf<S>::type P2;
+    constexpr uint32_t E = sizeof(P2);
+    if (item == 0 && threadIdx.x == 0) *a.ctr_out = *a.ctr_in + 1u;
+    Here h;
+    if (!here(a, item, h)) return;
+    uint32_t step = 0;  // seeds the stochastic rounding of 16-bit shares
+    if constexpr (sizeof(S) == 2) step = *a.ctr_in;
+    const Near ar = near(a, h);
+    float F[3], mv[kSplitMoments];
+    GeoMom<S, false>::get(a.mom, a.pitch, h.n, 0u, mv);
+    split_gradient<true>(a.psi, a.pitch, ar, F);
+    PostOut<L, float> o;
+    split_collide(a.mo, mv, F, o);
+    const __amdgpu_buffer_rsrc_t rout = state_rsrc(static_cast<S *>(a.out), uint32_t(L::Q) * a.pitch * E);
+    // Half-way bounce-back: where link i comes from a wall, the new pair of
+    // the opposite direction is also stored in the wall node's slot.  Waves
+    // with no wall link skip it.
+    const uint32_t wall = (h.lk & kLinkBits) ? wall_links(a, h.lk, ar) : 0u;
+    const bool walls = __builtin_amdgcn_ballot_w64(wall != 0u) != 0;
+    IoLinks<S> io(a, h, wall);
+    if (io.outlets(h)) {
+        // the moments of the pairs before they are stored below (16-bit
+        // storage: with the same random bits)
+        Dither dz(step, h.n);
+        OwnSum<L, S, float> sum;
+#pragma unroll
+        for (int j = 0; j < L::Q; ++j)
+            sum.add(j, encode_step<L, S, float>(o.df[j], o.mm[j], (o.red >> j) & 1u, j, dz));
+        io.om = sum.moments();
+    }
+    Dither dz(step, h.n);
+#pragma unroll
+    for (int j = 0; j < L::Q; ++j) {
+        const P2 v = encode_step<L, S, float>(o.df[j], o.mm[j], (o.red >> j) & 1u, j, dz);
+        store_pair<P2>(rout, h.n * E, uint32_t(su(uint32_t(j) * a.pitch * E)), v);
+        if (j == 0) continue;
+        const int i = L::opp[j];
+        if (walls && ((wall >> i) & 1u))
+            store_pair<P2>(rout, ar.vo(i) * E, uint32_t(su(uint32_t(i) * a.pitch * E)), v);
+        io.put(a, h, ar, rout, i, v);
+    }
+}
+
+template <typename S, bool COMPACT>
+__global__ void __launch_bounds__(kGeoBlock) k_geo_moments(SplitDesc a) {
+    geo_moments<S, COMPACT>(a, blockIdx.x);
+}
+template <typename S>
+__global__ void __launch_bounds__(kGeoBlock) k_geo_collide(SplitDesc a) {
+    geo_collide<S>(a, blockIdx.x);
+}
+// Many lattices in one launch.
+template <typename S>
+__global__ void __launch_bounds__(kGeoBlock) k_geo_moments_batch(const SplitDesc *__restrict__ desc,
+                                                                const LatMap *__restrict__ map) {
+    uint32_t item;
+    const SplitDesc a = desc[find_lat(*map, blockIdx.x, item)];
+    geo_moments<S, false>(a, item);
+}
+template <typename S>
+__global__ void __launch_bounds__(kGeoBlock) k_geo_collide_batch(const SplitDesc *__restrict__ desc,
+                                                                const LatMap *__restrict__ map) {
+    uint32_t item;
+    const SplitDesc a = desc[find_lat(*map, blockIdx.x, item)];
+    geo_collide<S>(a, item);
 }
 
 // ------------------------------------------------------------ compact state
@@ -429,11 +365,10 @@ __global__ void __launch_bounds__(kIoBlock) k_geo_boundary(SplitArgs<S> sa, Mode
 // that the boundary kernel stored in that node's slot of a pair buffer (the
 // values of the pair-state step, formed from the node's own new
 // populations).
-template <typename S>
 struct CGeoArgs {
-    SplitArgs<S> s;      // s.a.in: pair buffer read (inlet and outlet values), s.a.out: pair buffer written
-    const uint8_t *cin;  // compact state read
-    uint8_t *cout;       // compact state written
+    SplitDesc s;      // s.in, s.out: compact state read and written
+    const void *gin;  // pair buffer read (inlet and outlet values)
+    void *gout;       // pair buffer written
 };
 template <typename S>
 constexpr uint32_t c_bytes() {  // bytes per node of the compact state
@@ -446,18 +381,22 @@ struct CRec {
     bool fl;
 };
 template <typename S>
-__device__ __forceinline__ CRec c_record(__amdgpu_buffer_rsrc_t rc, uint32_t u, uint32_t pitch) {
-    typedef CStore<S> St;
-    const uint32_t base = uint32_t(D3Q19::Q) * pitch * St::E;
-    const typename St::RawB rb = St::load_b(rc, u * St::kRecB, base + pitch * St::kRecA);
-    const f4 e = St::entry(St::load_a(rc, u * St::kRecA, base), rb);
+__device__ __forceinline__ CRec c_record_of(typename CStore<S>::RawA ra, typename CStore<S>::RawB rb) {
+    const f4 e = CStore<S>::entry(ra, rb);
     CRec c;
     c.M = Codec<float>::col<float>(e[0], c.fl);
     c.Va[0] = e[1];
     c.Va[1] = e[2];
     c.Va[2] = e[3];
-    c.Rd = St::ratio(rb);
+    c.Rd = CStore<S>::ratio(rb);
     return c;
+}
+template <typename S>
+__device__ __forceinline__ CRec c_record(__amdgpu_buffer_rsrc_t rc, uint32_t u, uint32_t pitch) {
+    typedef CStore<S> St;
+    const uint32_t base = uint32_t(D3Q19::Q) * pitch * St::E;
+    const typename St::RawB rb = St::load_b(rc, u * St::kRecB, base + pitch * St::kRecA);
+    return c_record_of<S>(St::load_a(rc, u * St::kRecA, base), rb);
 }
 // Total deviation f_i - w_i stored at element `at` of the totals (i * pitch
 // + node; a direction of the speed class of i).
@@ -486,18 +425,17 @@ __device__ __forceinline__ typename PairOf<S>::type c_pair(float d, int i, const
     return encode_pair<L, S, float>(d, keep ? q : 1.0f - q, keep ? r.fl : !r.fl, i);
 }
 
-// The node's own moments (density, red density, velocity) from its new
-// totals and record: own_moments of its populations, each split as a
-// receiver splits it (no division per population).
-template <typename S>
-__device__ __forceinline__ OwnMom<float> c_own_moments(__amdgpu_buffer_rsrc_t rc, uint32_t n, uint32_t pitch,
-                                                       const CRec &r) {
+// The node's own moments (density, red density, velocity) from its new totals
+// and record: own_moments of its populations, each split as a receiver splits
+// it (no division per population).
+template <class Tot>
+__device__ __forceinline__ OwnMom<float> c_own_moments(const CRec &r, Tot total) {
     using L = D3Q19;
     float drho = 0, Ra = 0, jx = 0, jy = 0, jz = 0;
     int K = 0;
 #pragma unroll
     for (int k = 0; k < L::Q; ++k) {
-        const float d = c_total<S>(rc, uint32_t(k) * pitch + n, k);
+        const float d = total(k);
         const float mu = r.M * (float(w36<L>(k)) + 36.0f * d) + c_vd(k, r);
         const float t = 36.0f * d - mu;
         drho += d;
@@ -518,177 +456,121 @@ __device__ __forceinline__ OwnMom<float> c_own_moments(__amdgpu_buffer_rsrc_t rc
 
 // Each link is one load of a total and one of a record (from the cache: a
 // record serves up to 19 receivers).  Staging the block's records with a
-// one-node halo in LDS first (66 x 6 x 3 per block) measured slower on the
-// 512 x 128 x 64 junction: 0.129 against 0.119 ms per step.
+// one-node halo in LDS first measured slower (0.129 against 0.119 ms on the
+// 512 x 128 x 64 junction).  A wave whose nodes have no non-fluid link takes
+// the periodic step's loads.
 template <typename S>
-__global__ void __launch_bounds__(kGeoBlock) k_cgeo_moments(CGeoArgs<S> ca) {
+__global__ void __launch_bounds__(kGeoBlock) k_cgeo_moments(CGeoArgs ca) {
     using L = D3Q19;
     typedef float T;
     typedef typename PairOf<S>::type P2;
     constexpr uint32_t E = sizeof(P2);
-    const FusedArgs<S> &a = ca.s.a;
+    const SplitDesc &a = ca.s;
     Here h;
-    if (!here(a.nx, a.ny, a.nz, ca.s.blocks[blockIdx.x], h)) return;
-    const uint32_t pitch = uint32_t(a.pitch);
-    const __amdgpu_buffer_rsrc_t rc = state_rsrc(ca.cin, c_bytes<S>() * pitch);
-    const uint32_t n = h.n;
-    const uint32_t clk = a.links[n];
-    if (!(clk & kLinkFluid)) return;
-    // links from walls and from inlets or outlets (a node whose non-fluid
-    // neighbours mix codes reads them from the mask)
-    uint32_t wall = 0;
-    if (clk & kLinkMixed) {
-#pragma unroll
-        for (int i = 1; i < L::Q; ++i)
-            if ((clk >> i) & 1u)
-                wall |= is_wall(a.mask[nbr(a.nx, a.ny, a.nz, h, -L::cx[i], -L::cy[i], -L::cz[i])]) ? (1u << i) : 0u;
-    } else if (is_wall(link_code(clk))) {
-        wall = clk & kLinkBits;
-    }
-    const uint32_t io = clk & kLinkBits & ~wall;
-    // Every link as a plain load with a per-lane address: from a fluid node
-    // its total of direction i and its record; from a wall the node's own
-    // total of the opposite direction and its own record, the recolouring
-    // term with the opposite sign.  Links from inlets and outlets are
-    // replaced below.
+    if (!here(a, banded(gridDim.x), h)) return;
+    const uint32_t pitch = a.pitch;
+    const Near ar = near(a, h);
     CPops<L, T> q;
-    q.red = 0;
+    if (__builtin_amdgcn_ballot_w64((h.lk & kLinkBits) != 0u) == 0) {
+        pull_compact<S>(a.in, pitch, ar, q);
+    } else {
+        const __amdgpu_buffer_rsrc_t rc = state_rsrc(static_cast<const uint8_t *>(a.in), c_bytes<S>() * pitch);
+        // links from walls and from inlets or outlets
+        const uint32_t wall = (h.lk & kLinkBits) ? wall_links(a, h.lk, ar) : 0u;
+        const uint32_t io = h.lk & kLinkBits & ~wall;
+        // Every link as a plain load with a per-lane address: from a fluid
+        // node its total of direction i and its record; from a wall the node's
+        // own total of the opposite direction and its own record, the
+        // recolouring term with the opposite sign.  Links from inlets and
+        // outlets are replaced below.
+        q.red = 0;
 #pragma unroll
-    for (int i = 0; i < L::Q; ++i) {
-        const bool wl = (wall >> i) & 1u;
-        const uint32_t u = nbr(a.nx, a.ny, a.nz, h, -L::cx[i], -L::cy[i], -L::cz[i]);
-        const uint32_t src = wl ? uint32_t(L::opp[i]) * pitch + n : uint32_t(i) * pitch + u;
-        const float d = c_total<S>(rc, src, i);
-        const CRec r = c_record<S>(rc, wl ? n : u, pitch);
-        const float vd = c_vd(i, r);
-        q.df[i] = d;
-        q.mm[i] = r.M;
-        q.vd[i] = wl ? -vd : vd;
-        q.red |= r.fl ? (1u << i) : 0u;
-    }
-    if (io) {
-        const __amdgpu_buffer_rsrc_t rg = state_rsrc(a.in, uint32_t(L::Q) * pitch * E);
+        for (int i = 0; i < L::Q; ++i) {
+            const bool wl = (wall >> i) & 1u;
+            const uint32_t u = ar.vo(i);
+            const uint32_t src = wl ? uint32_t(L::opp[i]) * pitch + h.n : uint32_t(i) * pitch + u;
+            const float d = c_total<S>(rc, src, i);
+            const CRec r = c_record<S>(rc, wl ? h.n : u, pitch);
+            const float vd = c_vd(i, r);
+            q.df[i] = d;
+            q.mm[i] = r.M;
+            q.vd[i] = wl ? -vd : vd;
+            q.red |= r.fl ? (1u << i) : 0u;
+        }
+        if (io) {
+            const __amdgpu_buffer_rsrc_t rg = state_rsrc(static_cast<const S *>(ca.gin), uint32_t(L::Q) * pitch * E);
 #pragma unroll
-        for (int i = 1; i < L::Q; ++i) {
-            if (!((io >> i) & 1u)) continue;
-            const uint32_t u = nbr(a.nx, a.ny, a.nz, h, -L::cx[i], -L::cy[i], -L::cz[i]);
-            const P2 v = load_pair<P2>(rg, u * E, uniform(int(uint32_t(i) * pitch * E)));
-            bool fl;
-            q.df[i] = Codec<S>::template df<L, T>(v.x, i);
-            q.mm[i] = Codec<S>::template col<T>(v.y, fl);
-            q.vd[i] = 0.0f;
-            q.red = fl ? (q.red | (1u << i)) : (q.red & ~(1u << i));
+            for (int i = 1; i < L::Q; ++i) {
+                if (!((io >> i) & 1u)) continue;
+                const P2 v = load_pair<P2>(rg, ar.vo(i) * E, uint32_t(su(uint32_t(i) * pitch * E)));
+                bool fl;
+                q.df[i] = Codec<S>::template df<L, T>(v.x, i);
+                q.mm[i] = Codec<S>::template col<T>(v.y, fl);
+                q.vd[i] = 0.0f;
+                q.red = fl ? (q.red | (1u << i)) : (q.red & ~(1u << i));
+            }
         }
     }
     Mom<T> mm;
     moments<L, T>(q, mm);
-    ca.s.psi[n] = float(psi_of<T>(mm.drho, mm.r36R, mm.r36B));
-    const float vals[kNM] = {mm.drho, mm.r36R, mm.r36B, mm.j[0], mm.j[1], mm.j[2],
-                             mm.S[0], mm.S[1], mm.S[2], mm.S[3], mm.S[4], mm.S[5]};
-#pragma unroll
-    for (int k = 0; k < kNM; ++k) ca.s.mom[int64_t(k) * a.pitch + n] = vals[k];
+    geo_put<S, true>(a, h, mm);
 }
 
 template <typename S>
-__global__ void __launch_bounds__(kGeoBlock) k_cgeo_collide(CGeoArgs<S> ca, Model<float> mo) {
+__global__ void __launch_bounds__(kGeoBlock) k_cgeo_collide(CGeoArgs ca) {
     using L = D3Q19;
-    typedef float T;
-    const FusedArgs<S> &a = ca.s.a;
+    typedef CStore<S> St;
+    const SplitDesc &a = ca.s;
     if (blockIdx.x == 0 && threadIdx.x == 0) *a.ctr_out = *a.ctr_in + 1u;
-    if (!ca.s.blocks) return;  // no fluid node
     Here h;
-    if (!here(a.nx, a.ny, a.nz, ca.s.blocks[blockIdx.x], h)) return;
-    const uint32_t n = h.n;
-    const uint32_t clk = a.links[n];
-    if (!(clk & kLinkFluid)) return;
-    const uint32_t step = *a.ctr_in;  // seeds the stochastic rounding of FP16 storage
-    const float pc = ca.s.psi[n];
-    T fx = 0, fy = 0, fz = 0;
-#pragma unroll
-    for (int i = 1; i < L::Q; ++i) {
-        const uint32_t m = nbr(a.nx, a.ny, a.nz, h, L::cx[i], L::cy[i], L::cz[i]);
-        const float pv = ((clk >> L::opp[i]) & 1u) ? solid_psi(a, a.mask[m], pc) : ca.s.psi[m];
-        const T wp = T(3.0 * wgt<L>(i)) * T(pv);
-        if (L::cx[i]) fx += L::cx[i] > 0 ? wp : -wp;
-        if (L::cy[i]) fy += L::cy[i] > 0 ? wp : -wp;
-        if (L::cz[i]) fz += L::cz[i] > 0 ? wp : -wp;
-    }
-    const T F[3] = {fx, fy, fz};
-    T mv[kNM];
-#pragma unroll
-    for (int k = 0; k < kNM; ++k) mv[k] = ca.s.mom[int64_t(k) * a.pitch + n];
-    const T cj[3] = {mv[3], mv[4], mv[5]}, cS[6] = {mv[6], mv[7], mv[8], mv[9], mv[10], mv[11]};
-    CompactOut<L, T> o;
-    collide<L, T>(mo, mv[0], mv[1], mv[2], cj, cS, F, nullptr, o);
-    const uint32_t pitch = uint32_t(a.pitch);
-    const __amdgpu_buffer_rsrc_t rout = state_rsrc(ca.cout, c_bytes<S>() * pitch);
-    // the node's totals at byte n E of each array, its records at n kRecA
-    // and n kRecB (the periodic sweep's store, with the plane offset 0)
-    CStore<S>::store(rout, n * CStore<S>::E, 0u, pitch, o, step);
+    if (!here(a, banded(gridDim.x), h)) return;
+    uint32_t step = 0;  // seeds the stochastic rounding of FP16 storage
+    if constexpr (sizeof(S) == 2) step = *a.ctr_in;
+    const Near ar = near(a, h);
+    float F[3], mv[kSplitMoments];
+    GeoMom<S, true>::get(a.mom, a.pitch, h.n, 0u, mv);
+    split_gradient<true>(a.psi, a.pitch, ar, F);
+    CompactOut<L, float> o;
+    split_collide(a.mo, mv, F, o);
+    const __amdgpu_buffer_rsrc_t rout = state_rsrc(static_cast<uint8_t *>(a.out), c_bytes<S>() * a.pitch);
+    St::put(rout, h.n * St::E, 0u, a.pitch, St::encode(o, step, h.n));
 }
 
-// Inlet and outlet values on the compact state: as k_geo_boundary (a wave
-// per direction and 64 listed nodes), from the node's new totals and record.
-template <int I, typename S>
-__device__ __forceinline__ void cio_link(const CGeoArgs<S> &ca, const Model<float> &mo, uint32_t n, uint32_t so_i) {
+// Inlet and outlet values from the stored totals and record of the node that
+// pulls them: thread k takes one link direction I of entry k of the list of
+// nodes with such links.
+template <typename S, int I>
+__device__ __forceinline__ void io_link(const CGeoArgs &ca, uint32_t dir, uint32_t n, uint32_t lk) {
     using L = D3Q19;
-    typedef float T;
-    typedef typename PairOf<S>::type P2;
-    constexpr uint32_t E = sizeof(P2);
-    const FusedArgs<S> &a = ca.s.a;
-    const uint32_t clk = a.links[n];
-    if (!((clk >> I) & 1u)) return;
-    Here h;
-    const uint32_t t = n / uint32_t(a.nx);
-    h.n = n;
-    h.x = int(n - t * uint32_t(a.nx));
-    h.z = int(t / uint32_t(a.ny));
-    h.y = int(t - uint32_t(h.z) * uint32_t(a.ny));
-    const uint32_t m = nbr(a.nx, a.ny, a.nz, h, -L::cx[I], -L::cy[I], -L::cz[I]);
-    const uint8_t c = (clk & kLinkMixed) ? a.mask[m] : link_code(clk);
-    if (is_wall(c)) return;
-    const uint32_t pitch = uint32_t(a.pitch);
-    const __amdgpu_buffer_rsrc_t rc = state_rsrc(ca.cout, c_bytes<S>() * pitch);
-    const __amdgpu_buffer_rsrc_t rg = state_rsrc(a.out, uint32_t(L::Q) * pitch * E);
-    const CRec own = c_record<S>(rc, n, pitch);
-    Geo g{};
-    g.inlets = a.inlets;
-    g.outlets = a.outlets;
-    OwnMom<T> om{};
-    if (c >= kOutlet0) om = c_own_moments<S>(rc, n, pitch, own);
-    const P2 ov = c_pair<S>(c_total<S>(rc, uint32_t(L::opp[I]) * pitch + n, L::opp[I]), L::opp[I], own);
-    store_pair<P2>(rg, m * E, uint32_t(uniform(int(so_i))),
-                   boundary_pair_v<L, S, T>(mo, I, c, io_vals<T>(g, c), ov, om));
-}
-
-template <typename S>
-__global__ void __launch_bounds__(kIoBlock) k_cgeo_boundary(CGeoArgs<S> ca, Model<float> mo, uint32_t count) {
-    constexpr uint32_t E = sizeof(typename PairOf<S>::type);
-    const uint32_t b = blockIdx.x, chunk = b / 18u, dir = 1u + (b - chunk * 18u);
-    const uint32_t so_i = dir * uint32_t(ca.s.a.pitch) * E;
-    const uint32_t k = chunk * kIoBlock + threadIdx.x;
-    if (k >= count) return;
-    const uint32_t n = ca.s.blocks[k];
-    switch (dir) {
-        case 1: cio_link<1, S>(ca, mo, n, so_i); break;
-        case 2: cio_link<2, S>(ca, mo, n, so_i); break;
-        case 3: cio_link<3, S>(ca, mo, n, so_i); break;
-        case 4: cio_link<4, S>(ca, mo, n, so_i); break;
-        case 5: cio_link<5, S>(ca, mo, n, so_i); break;
-        case 6: cio_link<6, S>(ca, mo, n, so_i); break;
-        case 7: cio_link<7, S>(ca, mo, n, so_i); break;
-        case 8: cio_link<8, S>(ca, mo, n, so_i); break;
-        case 9: cio_link<9, S>(ca, mo, n, so_i); break;
-        case 10: cio_link<10, S>(ca, mo, n, so_i); break;
-        case 11: cio_link<11, S>(ca, mo, n, so_i); break;
-        case 12: cio_link<12, S>(ca, mo, n, so_i); break;
-        case 13: cio_link<13, S>(ca, mo, n, so_i); break;
-        case 14: cio_link<14, S>(ca, mo, n, so_i); break;
-        case 15: cio_link<15, S>(ca, mo, n, so_i); break;
-        case 16: cio_link<16, S>(ca, mo, n, so_i); break;
-        case 17: cio_link<17, S>(ca, mo, n, so_i); break;
-        default: cio_link<18, S>(ca, mo, n, so_i); break;
+    if constexpr (I < L::Q) {
+        if (dir != I) return io_link<S, I + 1>(ca, dir, n, lk);  // uniform over the block
+        typedef typename PairOf<S>::type P2;
+        constexpr uint32_t E = sizeof(P2);
+        if (!((lk >> I) & 1u)) return;
+        const SplitDesc &a = ca.s;
+        const uint32_t u = near(a, node_at(a, n, lk)).vo(I);
+        const uint8_t c = (lk & kLinkMixed) ? a.mask[u] : link_code(lk);
+        if (is_wall(c)) return;
+        const uint32_t pitch = a.pitch;
+        const __amdgpu_buffer_rsrc_t rc = state_rsrc(static_cast<const uint8_t *>(a.out), c_bytes<S>() * pitch);
+        const CRec own = c_record<S>(rc, n, pitch);
+        OwnMom<float> om{};
+        if (c >= kOutlet0) om = c_own_moments(own, [&](int k) { return c_total<S>(rc, uint32_t(k) * pitch + n, k); });
+        const P2 v = c_pair<S>(c_total<S>(rc, uint32_t(L::opp[I]) * pitch + n, L::opp[I]), L::opp[I], own);
+        Geo g{};
+        g.inlets = a.inlets;
+        g.outlets = a.outlets;
+        store_pair<P2>(state_rsrc(static_cast<S *>(ca.gout), uint32_t(L::Q) * pitch * E), u * E,
+                       uint32_t(su(uint32_t(I) * pitch * E)),
+                       boundary_pair_v<L, S, float>(a.mo, I, c, io_vals<float>(g, c), v, om));
     }
+}
+template <typename S>
+__global__ void __launch_bounds__(kIoBlock) k_cgeo_boundary(CGeoArgs ca) {
+    const uint32_t k = blockIdx.x * kIoBlock + threadIdx.x;
+    if (k >= ca.s.count) return;
+    const uint2 e = reinterpret_cast<const uint2 *>(ca.s.list)[k];
+    io_link<S, 1>(ca, blockIdx.y + 1u, e.x, e.y);
 }
 
 // The compact state of the fluid nodes as pairs, for reads of the state:
@@ -696,189 +578,166 @@ __global__ void __launch_bounds__(kIoBlock) k_cgeo_boundary(CGeoArgs<S> ca, Mode
 // bounce-back values in the wall nodes' slots; the inlet and outlet values
 // are already in the pair buffer.
 template <typename S>
-__global__ void __launch_bounds__(kGeoBlock) k_cgeo_expand(CGeoArgs<S> ca) {
+__global__ void __launch_bounds__(kGeoBlock) k_cgeo_expand(CGeoArgs ca) {
     using L = D3Q19;
     typedef typename PairOf<S>::type P2;
     constexpr uint32_t E = sizeof(P2);
-    const FusedArgs<S> &a = ca.s.a;
+    const SplitDesc &a = ca.s;
     Here h;
-    if (!here(a.nx, a.ny, a.nz, ca.s.blocks[blockIdx.x], h)) return;
-    const uint32_t n = h.n;
-    const uint32_t clk = a.links[n];
-    if (!(clk & kLinkFluid)) return;
-    const uint32_t pitch = uint32_t(a.pitch);
-    const __amdgpu_buffer_rsrc_t rc = state_rsrc(ca.cin, c_bytes<S>() * pitch);
-    const __amdgpu_buffer_rsrc_t rg = state_rsrc(a.out, uint32_t(L::Q) * pitch * E);
-    const CRec own = c_record<S>(rc, n, pitch);
-    P2 ov[L::Q];
+    if (!here(a, banded(gridDim.x), h)) return;
+    const uint32_t pitch = a.pitch;
+    const Near ar = near(a, h);
+    const __amdgpu_buffer_rsrc_t rc = state_rsrc(static_cast<const uint8_t *>(a.in), c_bytes<S>() * pitch);
+    const __amdgpu_buffer_rsrc_t rg = state_rsrc(static_cast<S *>(ca.gout), uint32_t(L::Q) * pitch * E);
+    const CRec own = c_record<S>(rc, h.n, pitch);
+    const uint32_t wall = (h.lk & kLinkBits) ? wall_links(a, h.lk, ar) : 0u;
 #pragma unroll
     for (int j = 0; j < L::Q; ++j) {
-        ov[j] = c_pair<S>(c_total<S>(rc, uint32_t(j) * pitch + n, j), j, own);
-        store_pair<P2>(rg, n * E, uint32_t(uniform(int(uint32_t(j) * pitch * E))), ov[j]);
-    }
-#pragma unroll
-    for (int i = 1; i < L::Q; ++i) {
-        if (!((clk >> i) & 1u)) continue;
-        const uint32_t m = nbr(a.nx, a.ny, a.nz, h, -L::cx[i], -L::cy[i], -L::cz[i]);
-        if (is_wall((clk & kLinkMixed) ? a.mask[m] : link_code(clk)))
-            store_pair<P2>(rg, m * E, uint32_t(uniform(int(uint32_t(i) * pitch * E))), ov[L::opp[i]]);
+        const P2 v = c_pair<S>(c_total<S>(rc, uint32_t(j) * pitch + h.n, j), j, own);
+        store_pair<P2>(rg, h.n * E, uint32_t(su(uint32_t(j) * pitch * E)), v);
+        const int i = L::opp[j];
+        if (j != 0 && ((wall >> i) & 1u))
+            store_pair<P2>(rg, ar.vo(i) * E, uint32_t(su(uint32_t(i) * pitch * E)), v);
     }
 }
 
+// Whether a lattice and its plan fit the kernels (32-bit byte offsets must
+// cover a pair state).
+bool geo_ok(int prec, const Geo &g, const ModelD &md, const SplitPlan &sp) {
+    if (md.bgk || !g.mask || !g.links || (prec != 1 && prec != 2)) return false;
+    if (uint64_t(2 * D3Q19::Q) * uint64_t(g.pitch) * (prec == 1 ? 4u : 2u) >= (uint64_t(1) << 32)) return false;
+    return sp.fluid >= 0 && sp.fluid <= g.N && sp.io >= 0 && sp.io <= sp.fluid;
+}
+
 template <typename S>
-hipError_t run_cgeo(const Geo &g, const ModelD &md, bool pair_in, const void *in, const void *gin, void *cout,
-                    void *gout, void *psi, void *scratch, const SplitPlan &sp, const uint32_t *ctr_in,
-                    uint32_t *ctr_out, hipStream_t s) {
-    typedef typename PairOf<S>::type P2;
-    if (md.bgk || !g.mask || !g.links || !psi || !scratch) return hipErrorInvalidValue;
-    if (uint64_t(D3Q19::Q) * uint64_t(g.pitch) * sizeof(P2) >= (uint64_t(1) << 32)) return hipErrorInvalidValue;
-    const int64_t nb = split_blocks(g.nx, g.ny, g.nz);
-    if (nb <= 0 || nb > 0x7fffffff || sp.active > nb || sp.io > nb || sp.active < 0 || sp.io < 0 ||
-        sp.ionodes < 0 || sp.ionodes > g.pitch || (sp.ionodes > 0) != (sp.io > 0))
-        return hipErrorInvalidValue;
-    const ScratchMap m = scratch_map(scratch, g.pitch, nb);
-    CGeoArgs<S> ca;
-    // the pair buffer read: the pair state on a first step (pulled as pairs)
-    // or the inlet and outlet values; the pair buffer written: those values
-    ca.s.a = fused_args<S>(g, pair_in ? in : gin, gout, ctr_in, ctr_out, FusedShape{8, 1});
-    ca.s.psi = static_cast<float *>(psi);
-    ca.s.mom = m.mom;
-    ca.s.blocks = m.act;
-    ca.cin = static_cast<const uint8_t *>(in);
-    ca.cout = static_cast<uint8_t *>(cout);
-    const Model<float> mo = to_model<float>(md);
-    if (sp.active > 0) {
-        if (pair_in)
-            hipLaunchKernelGGL(k_geo_moments<S>, dim3(unsigned(sp.active)), dim3(kGeoBlock), 0, s, ca.s);
-        else
-            hipLaunchKernelGGL(k_cgeo_moments<S>, dim3(unsigned(sp.active)), dim3(kGeoBlock), 0, s, ca);
-    }
-    if (sp.active == 0) ca.s.blocks = nullptr;
-    hipLaunchKernelGGL(k_cgeo_collide<S>, dim3(unsigned(sp.active > 0 ? sp.active : 1)), dim3(kGeoBlock), 0, s, ca,
-                       mo);
-    ca.s.blocks = m.ionodes;
-    if (sp.ionodes > 0)
-        hipLaunchKernelGGL(k_cgeo_boundary<S>, dim3(unsigned(18 * ((sp.ionodes + kIoBlock - 1) / kIoBlock))),
-                           dim3(kIoBlock), 0, s, ca, mo, uint32_t(sp.ionodes));
+hipError_t run_split(const SplitDesc &a, hipStream_t s) {
+    hipLaunchKernelGGL((k_geo_moments<S, false>), dim3(a.nblocks), dim3(kGeoBlock), 0, s, a);
+    hipLaunchKernelGGL(k_geo_collide<S>, dim3(a.nblocks), dim3(kGeoBlock), 0, s, a);
     return hipGetLastError();
 }
 
 template <typename S>
-hipError_t run_expand_cgeo(const Geo &g, const void *cin, void *pout, void *scratch, const SplitPlan &sp,
-                           hipStream_t s) {
-    if (!g.mask || !g.links || !scratch) return hipErrorInvalidValue;
-    const int64_t nb = split_blocks(g.nx, g.ny, g.nz);
-    if (nb <= 0 || nb > 0x7fffffff || sp.active > nb || sp.active < 0) return hipErrorInvalidValue;
-    if (sp.active == 0) return hipSuccess;
-    const ScratchMap m = scratch_map(scratch, g.pitch, nb);
-    CGeoArgs<S> ca;
-    ca.s.a = fused_args<S>(g, nullptr, pout, nullptr, nullptr, FusedShape{8, 1});
-    ca.s.psi = nullptr;
-    ca.s.mom = nullptr;
-    ca.s.blocks = m.act;
-    ca.cin = static_cast<const uint8_t *>(cin);
-    ca.cout = nullptr;
-    hipLaunchKernelGGL(k_cgeo_expand<S>, dim3(unsigned(sp.active)), dim3(kGeoBlock), 0, s, ca);
+hipError_t run_cgeo(CGeoArgs ca, bool pair_in, const uint32_t *io, uint32_t nio, hipStream_t s) {
+    const SplitDesc &a = ca.s;
+    if (pair_in)
+        hipLaunchKernelGGL((k_geo_moments<S, true>), dim3(a.nblocks), dim3(kGeoBlock), 0, s, a);
+    else
+        hipLaunchKernelGGL(k_cgeo_moments<S>, dim3(a.nblocks), dim3(kGeoBlock), 0, s, ca);
+    hipLaunchKernelGGL(k_cgeo_collide<S>, dim3(a.nblocks), dim3(kGeoBlock), 0, s, ca);
+    if (nio > 0) {
+        ca.s.list = io;
+        ca.s.count = nio;
+        hipLaunchKernelGGL(k_cgeo_boundary<S>, dim3((nio + kIoBlock - 1) / kIoBlock, D3Q19::Q - 1), dim3(kIoBlock), 0,
+                           s, ca);
+    }
     return hipGetLastError();
 }
 
 template <typename S>
-hipError_t run_split(const Geo &g, const ModelD &md, const void *in, void *out, float *psi, void *scratch,
-                     const SplitPlan &sp, const uint32_t *ctr_in, uint32_t *ctr_out, hipStream_t s) {
-    typedef typename PairOf<S>::type P2;
-    if (!g.mask || !g.links || !psi || !scratch) return hipErrorInvalidValue;
-    if (uint64_t(D3Q19::Q) * uint64_t(g.pitch) * sizeof(P2) >= (uint64_t(1) << 32)) return hipErrorInvalidValue;
-    const int64_t nb = split_blocks(g.nx, g.ny, g.nz);
-    if (nb <= 0 || nb > 0x7fffffff || sp.active > nb || sp.io > nb || sp.active < 0 || sp.io < 0)
-        return hipErrorInvalidValue;
-    if (sp.ionodes < 0 || sp.ionodes > g.pitch || (sp.ionodes > 0) != (sp.io > 0)) return hipErrorInvalidValue;
-    const ScratchMap m = scratch_map(scratch, g.pitch, nb);
-    SplitArgs<S> sa;
-    sa.a = fused_args<S>(g, in, out, ctr_in, ctr_out, FusedShape{8, 1});
-    sa.psi = psi;
-    sa.mom = m.mom;
-    const Model<float> mo = to_model<float>(md);
-    sa.blocks = m.act;
-    if (sp.active > 0) hipLaunchKernelGGL(k_geo_moments<S>, dim3(unsigned(sp.active)), dim3(kGeoBlock), 0, s, sa);
-    // one block at least: it advances the step counter
-    if (sp.active == 0) sa.blocks = nullptr;
-    hipLaunchKernelGGL(k_geo_collide<S>, dim3(unsigned(sp.active > 0 ? sp.active : 1)), dim3(kGeoBlock), 0, s, sa,
-                       mo);
-    sa.blocks = m.ionodes;
-    if (sp.ionodes > 0)
-        hipLaunchKernelGGL(k_geo_boundary<S>, dim3(unsigned(18 * ((sp.ionodes + kIoBlock - 1) / kIoBlock))),
-                           dim3(kIoBlock), 0, s, sa, mo, uint32_t(sp.ionodes));
+hipError_t run_batch(const SplitDesc *desc, const LatMap *map, uint32_t blocks, hipStream_t s) {
+    hipLaunchKernelGGL(k_geo_moments_batch<S>, dim3(blocks), dim3(kGeoBlock), 0, s, desc, map);
+    hipLaunchKernelGGL(k_geo_collide_batch<S>, dim3(blocks), dim3(kGeoBlock), 0, s, desc, map);
     return hipGetLastError();
 }
 
 }  // namespace
 
-int64_t split_blocks(int nx, int ny, int nz) {
-    return int64_t((nx + kGX - 1) / kGX) * ((ny + kGY - 1) / kGY) * nz;
-}
-
-size_t split_scratch_bytes(int64_t pitch, int nx, int ny, int nz) {
-    const int64_t nb = split_blocks(nx, ny, nz);
-    return align256(sizeof(float) * kNM * size_t(pitch)) + align256(size_t(nb)) + align256(sizeof(uint16_t) * size_t(nb)) +
-           3 * align256(sizeof(uint32_t) * size_t(nb)) + align256(sizeof(uint32_t) * size_t(pitch)) +
-           align256(3 * sizeof(uint32_t));
+// (The size is that of the moments, a node list and the counts, which callers
+// plan their memory by; the lists and psi take 20 bytes of it.)
+size_t split_scratch_bytes(int64_t pitch) {
+    const size_t chunks = size_t((pitch + kChunk - 1) / kChunk);
+    return align256(sizeof(float) * kSplitMoments * size_t(pitch)) + align256(sizeof(uint32_t) * size_t(pitch)) +
+           align256(2 * sizeof(uint32_t) * chunks) + align256(sizeof(uint32_t));
 }
 
 hipError_t split_prepare(const Geo &g, void *scratch, SplitPlan &sp, hipStream_t s) {
     sp = SplitPlan{};
-    if (!g.links || !scratch) return hipErrorInvalidValue;
-    const int64_t nb = split_blocks(g.nx, g.ny, g.nz);
-    if (nb <= 0 || nb > 0x7fffffff) return hipErrorInvalidValue;
-    const ScratchMap m = scratch_map(scratch, g.pitch, nb);
-    hipLaunchKernelGGL(k_geo_flags, dim3(unsigned(nb)), dim3(kGeoBlock), 0, s, g.links, g.nx, g.ny, g.nz, m.flags,
-                       m.ioc);
-    hipLaunchKernelGGL(k_geo_lists, dim3(1), dim3(kListThreads), 0, s, m.flags, m.ioc, uint32_t(nb), m.act, m.io,
-                       m.ioofs, m.counts);
+    if (!g.links || !g.mask || !scratch) return hipErrorInvalidValue;
+    const ScratchMap m = scratch_map(scratch, g.pitch);
+    const uint32_t N = uint32_t(g.N), chunks = uint32_t((g.N + kChunk - 1) / kChunk);
+    uint32_t *none = nullptr;
+    hipLaunchKernelGGL(k_geo_solid_psi, dim3(unsigned((g.N + kGeoBlock - 1) / kGeoBlock)), dim3(kGeoBlock), 0, s, g,
+                       m.psi);
+    hipLaunchKernelGGL(k_geo_list, dim3(chunks), dim3(kGeoBlock), 0, s, g.links, N, m.counts, none, none);
+    hipLaunchKernelGGL(k_geo_scan, dim3(1), dim3(kScanThreads), 0, s, m.counts, chunks, m.totals);
+    hipLaunchKernelGGL(k_geo_list, dim3(chunks), dim3(kGeoBlock), 0, s, g.links, N, m.counts, m.list, m.io);
     hipError_t e = hipGetLastError();
-    uint32_t c[3] = {0, 0, 0};
-    if (e == hipSuccess) e = hipMemcpyAsync(c, m.counts, sizeof(c), hipMemcpyDeviceToHost, s);
+    uint32_t c[2] = {0, 0};
+    if (e == hipSuccess) e = hipMemcpyAsync(c, m.totals, sizeof(c), hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) return e;
-    if (int64_t(c[0]) > nb || int64_t(c[1]) > nb || int64_t(c[2]) > g.pitch || (c[1] > 0) != (c[2] > 0))
-        return hipErrorUnknown;
-    if (c[1] > 0) {
-        hipLaunchKernelGGL(k_geo_ionodes, dim3(c[1]), dim3(kGeoBlock), 0, s, g.links, g.nx, g.ny, g.nz, m.io, m.ioofs,
-                           m.ionodes);
-        e = hipGetLastError();
-        if (e == hipSuccess) e = hipStreamSynchronize(s);
-        if (e != hipSuccess) return e;
-    }
-    sp.active = c[0];
+    if (int64_t(c[0]) > g.N || c[1] > c[0]) return hipErrorUnknown;
+    sp.fluid = c[0];
     sp.io = c[1];
-    sp.ionodes = c[2];
     return hipSuccess;
 }
 
+SplitDesc split_desc(const Geo &g, const ModelD &md, const void *in, void *out, void *scratch, const SplitPlan &sp,
+                     const uint32_t *ctr_in, uint32_t *ctr_out) {
+    const ScratchMap m = scratch_map(scratch, g.pitch);
+    SplitDesc a{};
+    a.in = in;
+    a.out = out;
+    a.psi = m.psi;
+    a.mom = out;
+    a.nx = g.nx;
+    a.ny = g.ny;
+    a.nz = g.nz;
+    a.pitch = uint32_t(g.pitch);
+    a.list = m.list;
+    a.count = uint32_t(sp.fluid);
+    // one block at least: it advances the step counter
+    a.nblocks = uint32_t(sp.fluid > 0 ? (sp.fluid + kGeoBlock - 1) / kGeoBlock : 1);
+    a.div0 = fast_div(uint32_t(g.nx));
+    a.div1 = fast_div(uint32_t(g.ny));
+    a.ctr_in = ctr_in;
+    a.ctr_out = ctr_out;
+    a.mask = g.mask;
+    a.inlets = g.inlets;
+    a.outlets = g.outlets;
+    a.mo = to_model<float>(md);
+    return a;
+}
+
+hipError_t launch_step_split(int prec, const Geo &g, const ModelD &md, const void *in, void *out, void *scratch,
+                             const SplitPlan &sp, const uint32_t *ctr_in, uint32_t *ctr_out, hipStream_t s) {
+    if (!scratch || !geo_ok(prec, g, md, sp)) return hipErrorInvalidValue;
+    const SplitDesc a = split_desc(g, md, in, out, scratch, sp, ctr_in, ctr_out);
+    return prec == 1 ? run_split<float>(a, s) : run_split<_Float16>(a, s);
+}
+
+hipError_t launch_step_split_batch(int prec, const SplitDesc *desc, const LatMap *map, uint32_t blocks,
+                                   hipStream_t s) {
+    if (blocks == 0) return hipSuccess;
+    return prec == 1 ? run_batch<float>(desc, map, blocks, s) : run_batch<_Float16>(desc, map, blocks, s);
+}
+
 hipError_t launch_step_cgeo(int prec, const Geo &g, const ModelD &md, bool pair_in, const void *in, const void *gin,
-                            void *cout, void *gout, void *psi, void *scratch, const SplitPlan &sp,
-                            const uint32_t *ctr_in, uint32_t *ctr_out, hipStream_t s) {
-    if (prec == 1)
-        return run_cgeo<float>(g, md, pair_in, in, gin, cout, gout, psi, scratch, sp, ctr_in, ctr_out, s);
-    if (prec == 2)
-        return run_cgeo<_Float16>(g, md, pair_in, in, gin, cout, gout, psi, scratch, sp, ctr_in, ctr_out, s);
-    return hipErrorInvalidValue;
+                            void *cout, void *gout, void *scratch, const SplitPlan &sp, const uint32_t *ctr_in,
+                            uint32_t *ctr_out, hipStream_t s) {
+    if (!scratch || !geo_ok(prec, g, md, sp)) return hipErrorInvalidValue;
+    CGeoArgs ca;
+    ca.s = split_desc(g, md, in, cout, scratch, sp, ctr_in, ctr_out);
+    ca.gin = gin;
+    ca.gout = gout;
+    const uint32_t *io = scratch_map(scratch, g.pitch).io;
+    const uint32_t nio = uint32_t(sp.io);
+    return prec == 1 ? run_cgeo<float>(ca, pair_in, io, nio, s) : run_cgeo<_Float16>(ca, pair_in, io, nio, s);
 }
 
 hipError_t launch_expand_cgeo(int prec, const Geo &g, const void *cin, void *pout, void *scratch, const SplitPlan &sp,
                               hipStream_t s) {
-    if (prec == 1) return run_expand_cgeo<float>(g, cin, pout, scratch, sp, s);
-    if (prec == 2) return run_expand_cgeo<_Float16>(g, cin, pout, scratch, sp, s);
-    return hipErrorInvalidValue;
-}
-
-hipError_t launch_step_split(int prec, const Geo &g, const ModelD &md, const void *in, void *out, void *psi,
-                             void *scratch, const SplitPlan &sp, const uint32_t *ctr_in, uint32_t *ctr_out,
-                             hipStream_t s) {
-    if (md.bgk) return hipErrorInvalidValue;
-    float *p = static_cast<float *>(psi);
-    if (prec == 1) return run_split<float>(g, md, in, out, p, scratch, sp, ctr_in, ctr_out, s);
-    if (prec == 2) return run_split<_Float16>(g, md, in, out, p, scratch, sp, ctr_in, ctr_out, s);
-    return hipErrorInvalidValue;
+    if (!scratch || !geo_ok(prec, g, ModelD{}, sp)) return hipErrorInvalidValue;
+    if (sp.fluid == 0) return hipSuccess;
+    CGeoArgs ca;
+    ca.s = split_desc(g, ModelD{}, cin, nullptr, scratch, sp, nullptr, nullptr);
+    ca.gin = nullptr;
+    ca.gout = pout;
+    if (prec == 1)
+        hipLaunchKernelGGL(k_cgeo_expand<float>, dim3(ca.s.nblocks), dim3(kGeoBlock), 0, s, ca);
+    else
+        hipLaunchKernelGGL(k_cgeo_expand<_Float16>, dim3(ca.s.nblocks), dim3(kGeoBlock), 0, s, ca);
+    return hipGetLastError();
 }
 
 }  // namespace lbcg

@@ -104,51 +104,109 @@ bool fused_supported(int lattice, int prec, const Geo &g);
 // BGK form).
 int fused_resident_blocks(int prec, int rows, bool masked, bool pops = false);
 
-// Split D3Q19 step for lattices with geometry (F32 or F16 storage,
-// regularized): a moments kernel writes psi (`psi`, pitch floats) and the
-// kSplitMoments collision moments of every fluid node, a collision kernel
-// takes the gradient, collides and stores, and a boundary kernel stores the
-// inlet and outlet values.  Bitwise the column sweep's results; chosen by
-// FusedShape rows 0.  The moments and collision kernels run blocks of
-// kSplitGX x kSplitGY nodes of one z plane, only those with fluid, from a
-// block list; the boundary kernel runs one thread per node with links from
-// inlets or outlets, from a node list.  split_prepare builds the lists on the
-// device once per lattice in `scratch` (split_scratch_bytes: the moments,
-// then the lists).
+// Split D3Q19 steps (F32 or F16 storage, regularized): a moments kernel writes
+// psi and the kSplitMoments collision moments of every fluid node, a collision
+// kernel takes the gradient, collides and stores, with geometry the boundary
+// values too.  Bitwise the column sweeps' results.
 constexpr int kSplitMoments = 12;
-constexpr int kSplitGX = 64, kSplitGY = 4;
-int64_t split_blocks(int nx, int ny, int nz);
-size_t split_scratch_bytes(int64_t pitch, int nx, int ny, int nz);
-struct SplitPlan {
-    int64_t active = 0, io = 0;  // blocks with fluid, blocks with inlet or outlet links
-    int64_t ionodes = 0;         // nodes with inlet or outlet links
+constexpr int kBatchLatMax = 256;           // lattices of a batched split launch
+
+// Unsigned division by a constant of the launch: n / d = mulhi(n, mul) >> sh
+// for n < 2^31 (d > 1).  With s = floor(log2 d) and mul = ceil(2^(32 + s) / d)
+// the error mul d - 2^(32 + s) is below d < 2^(s + 1), so n < 2^31 divides
+// exactly; a power of two takes s - 1, whose mul is 2^31 exactly.
+struct FastDiv {
+    uint32_t d, mul, sh;
 };
-// Builds the block lists and returns their lengths (waits for the stream).
+inline FastDiv fast_div(uint32_t d) {
+    FastDiv f{d, 0, 0};
+    if (d <= 1) return f;
+    uint32_t s = 31u - uint32_t(__builtin_clz(d));
+    if ((d & (d - 1)) == 0) --s;
+    f.sh = s;
+    f.mul = uint32_t(((uint64_t(1) << (32 + s)) + d - 1) / d);
+    return f;
+}
+__device__ __forceinline__ uint32_t div_by(uint32_t n, const FastDiv &f) {
+    return f.d <= 1 ? n : __umulhi(n, f.mul) >> f.sh;
+}
+
+// Kernel view of one lattice for the split steps.  Periodic: blocks of 256
+// consecutive nodes of a plane (div0: blocks per plane, div1: nx); with
+// geometry: blocks of 256 entries of the list of fluid nodes (div0: nx, div1:
+// ny).
+struct SplitDesc {
+    const void *in;  // state read (pairs or compact)
+    void *out;       // state written
+    float *psi;      // psi of every node; with geometry what a non-fluid node shows the gradient
+    void *mom;       // moments, kSplitMoments floats per node
+    int nx, ny, nz;
+    uint32_t pitch;
+    uint32_t nblocks;  // of the moments and collision kernels
+    FastDiv div0, div1;
+    const uint32_t *ctr_in;
+    uint32_t *ctr_out;
+    // geometry
+    const uint32_t *list;  // fluid nodes {node, link word}
+    uint32_t count;
+    const uint8_t *mask;
+    const DevInlet *inlets;
+    const DevOutlet *outlets;
+    Model<float> mo;
+};
+
+// List of the fluid nodes of a lattice with geometry, built on the device once
+// per lattice in `scratch` (split_scratch_bytes).
+size_t split_scratch_bytes(int64_t pitch);
+struct SplitPlan {
+    int64_t fluid = 0;  // its length
+    int64_t io = 0;     // nodes with inlet or outlet links
+};
+// Builds the list and writes what the non-fluid nodes show the gradient into
+// the scratch's psi; returns the length (waits for the stream).
 hipError_t split_prepare(const Geo &g, void *scratch, SplitPlan &sp, hipStream_t s);
+
+// A step of one lattice.  Periodic: compact_in / compact_out: the state read /
+// written is compact (else pairs); mom (compact_out only; a pair step keeps
+// its moments in `out`): kSplitMoments * pitch floats.
+hipError_t launch_step_psplit(int prec, const Geo &g, const ModelD &md, const void *in, bool compact_in, void *out,
+                              bool compact_out, void *psi, void *mom, const uint32_t *ctr_in, uint32_t *ctr_out,
+                              hipStream_t s);
+hipError_t launch_step_split(int prec, const Geo &g, const ModelD &md, const void *in, void *out, void *scratch,
+                             const SplitPlan &sp, const uint32_t *ctr_in, uint32_t *ctr_out, hipStream_t s);
 // The split step on the compact state (D3Q19 F32 or F16 with geometry): reads the
 // compact state `in` (or, with pair_in, the pair state `in`, on the first
 // step after an initialisation or a restore), the inlet and outlet values in
 // the pair buffer gin, writes the compact state `cout` and the new inlet and
 // outlet values into the pair buffer gout.
 hipError_t launch_step_cgeo(int prec, const Geo &g, const ModelD &md, bool pair_in, const void *in, const void *gin,
-                            void *cout, void *gout, void *psi, void *scratch, const SplitPlan &sp,
-                            const uint32_t *ctr_in, uint32_t *ctr_out, hipStream_t s);
+                            void *cout, void *gout, void *scratch, const SplitPlan &sp, const uint32_t *ctr_in,
+                            uint32_t *ctr_out, hipStream_t s);
 // Its compact state as pairs (fluid nodes and wall values) into pout, which
 // already holds the inlet and outlet values.
 hipError_t launch_expand_cgeo(int prec, const Geo &g, const void *cin, void *pout, void *scratch, const SplitPlan &sp,
                               hipStream_t s);
-hipError_t launch_step_split(int prec, const Geo &g, const ModelD &md, const void *in, void *out, void *psi,
-                             void *scratch, const SplitPlan &sp, const uint32_t *ctr_in, uint32_t *ctr_out,
-                             hipStream_t s);
 
-// Split step of periodic D3Q19 lattices (F32 or F16 storage, regularized):
-// a moments kernel and a collision kernel, bitwise the sweeps' results.
-// compact_in / compact_out: the state read / written is compact (else
-// pairs); psi: pitch floats; mom (compact_out only; a pair step keeps its
-// moments in `out`): kSplitMoments * pitch floats.
-hipError_t launch_step_psplit(int prec, const Geo &g, const ModelD &md, const void *in, bool compact_in, void *out,
-                              bool compact_out, void *psi, void *mom, const uint32_t *ctr_in, uint32_t *ctr_out,
-                              hipStream_t s);
+bool psplit_supported(int prec, const Geo &g);
+
+// The same steps of many lattices, a launch per kernel: descriptors and block
+// maps in device memory.  A block map says which lattice a block belongs to:
+// block b is block b - start[q] of lattice lat[q] for the last q with start[q]
+// <= b.  A launch of start[k] blocks steps the first k lattices of the map.
+struct LatMap {
+    int n;
+    uint32_t start[kBatchLatMax + 1];
+    uint8_t lat[kBatchLatMax];
+};
+hipError_t launch_step_psplit_batch(int prec, bool compact, const SplitDesc *desc, const LatMap *map, uint32_t blocks,
+                                    hipStream_t s);
+hipError_t launch_step_split_batch(int prec, const SplitDesc *desc, const LatMap *map, uint32_t blocks, hipStream_t s);
+// Descriptors of one lattice's step (compact: periodic lattices on the compact
+// state; else the pair state).
+SplitDesc psplit_desc(const Geo &g, const ModelD &md, const void *in, void *out, bool compact, void *psi, void *mom,
+                      const uint32_t *ctr_in, uint32_t *ctr_out);
+SplitDesc split_desc(const Geo &g, const ModelD &md, const void *in, void *out, void *scratch, const SplitPlan &sp,
+                     const uint32_t *ctr_in, uint32_t *ctr_out);
 
 // Fused single-pass D2Q9 step over tiles (lbcg_tile2d.hip): F64, F32 or F16
 // storage, with or without geometry, any collision form.

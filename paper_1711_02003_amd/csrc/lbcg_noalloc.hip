@@ -32,7 +32,9 @@ constexpr int kMaxLat = LBCG_NOALLOC_MAX_LATTICES;
 constexpr int kMaxBlocks = LBCG_NOALLOC_MAX_BLOCKS;
 constexpr size_t kDescBytes = (2 * size_t(kMaxLat) * sizeof(Desc) + 255) / 256 * 256;
 constexpr size_t kTabBytes = 4 * size_t(kMaxBlocks) * sizeof(int);
-constexpr size_t kScratchBytes = kDescBytes + kTabBytes;  // ~1.1 MB
+constexpr size_t kSplitBytes = (2 * size_t(kMaxLat) * sizeof(SplitDesc) + 255) / 256 * 256;
+constexpr size_t kMapBytes = (sizeof(LatMap) + 255) / 256 * 256;
+constexpr size_t kScratchBytes = kDescBytes + kTabBytes + kSplitBytes + 2 * kMapBytes;  // ~1.2 MB
 constexpr int kDescPerFill = 8;
 constexpr int kMaxDevices = 64;
 constexpr int kTileX = 64;
@@ -45,6 +47,16 @@ struct DescFill {
 };
 static_assert(sizeof(DescFill) < 4000, "kernel argument size");
 static_assert(sizeof(Desc) % 4 == 0, "descriptor copied in 4-byte words");
+
+// The same of the split steps' descriptors.
+constexpr int kSplitPerFill = 6;
+struct SplitFill {
+    SplitDesc d[2][kSplitPerFill];
+    int lat[kSplitPerFill], count;
+};
+static_assert(sizeof(SplitFill) < 4000, "kernel argument size");
+static_assert(sizeof(SplitDesc) % 4 == 0 && sizeof(LatMap) % 4 == 0, "copied in 4-byte words");
+static_assert(kMaxLat <= kBatchLatMax, "block map size");
 
 // One group's block table: entries [start[q], start[q + 1]) are the work
 // items of lattice lat[q], q < n.
@@ -74,6 +86,21 @@ __global__ void __launch_bounds__(256) k_fill_desc(DescFill f, unsigned char *ar
         reinterpret_cast<uint32_t *>(&desc[size_t(par) * kMaxLat + f.first + j])[wd] =
             reinterpret_cast<const uint32_t *>(&f.d[par][j])[wd];
     }
+}
+
+__global__ void __launch_bounds__(256) k_fill_split(SplitFill f, SplitDesc *desc) {
+    constexpr int words = int(sizeof(SplitDesc) / 4);
+    const int per = f.count * words;
+    for (int k = int(threadIdx.x); k < 2 * per; k += int(blockDim.x)) {
+        const int par = k / per, r = k % per, j = r / words, wd = r % words;
+        reinterpret_cast<uint32_t *>(&desc[size_t(par) * kMaxLat + f.lat[j]])[wd] =
+            reinterpret_cast<const uint32_t *>(&f.d[par][j])[wd];
+    }
+}
+
+__global__ void __launch_bounds__(256) k_fill_map(LatMap m, LatMap *out) {
+    for (int k = int(threadIdx.x); k < int(sizeof(LatMap) / 4); k += int(blockDim.x))
+        reinterpret_cast<uint32_t *>(out)[k] = reinterpret_cast<const uint32_t *>(&m)[k];
 }
 
 __global__ void __launch_bounds__(256) k_fill_tab(TabFill t, int total, int *lat_out, int *item_out) {
@@ -207,8 +234,62 @@ extern "C" int lbcg_batch_step_noalloc(lbcg_sim *const *sims, int32_t n, const i
     }
     const hipStream_t st = s0->stream;
 
-    // descriptors of every lattice, in chunks of kDescPerFill per launch
-    for (int first = 0; first < n; first += kDescPerFill) {
+    // Each group (periodic, geometry) on the sweep or, where every member can
+    // take it and it is expected to be faster, on the split step.
+    bool split[2] = {true, true};
+    double sweep_us[2] = {0, 0}, split_us[2] = {0, 0};
+    for (int q = 0; q < k; ++q) {
+        const lbcg_sim *s = sims[order[q]];
+        const int m = s->g.mask != nullptr;
+        split[m] = split[m] && batch_split_ok(s);
+        double a = 0, b = 0;
+        batch_cost(s, a, b);
+        sweep_us[m] += a;
+        split_us[m] += b;
+    }
+    for (int m = 0; m < 2; ++m) split[m] = split[m] && split_us[m] < sweep_us[m];
+    SplitDesc *sdesc = reinterpret_cast<SplitDesc *>(area + kDescBytes + kTabBytes);
+    LatMap *maps[2];
+    for (int m = 0; m < 2; ++m)
+        maps[m] = reinterpret_cast<LatMap *>(area + kDescBytes + kTabBytes + kSplitBytes + size_t(m) * kMapBytes);
+    uint32_t sblocks[kMaxLat] = {};  // per lattice, on the split step
+    if (split[0] || split[1]) {
+        SplitFill f;
+        f.count = 0;
+        for (int q = 0; q <= k; ++q) {
+            if (q < k && !split[sims[order[q]]->g.mask != nullptr]) continue;
+            if (q < k) {
+                const int j = order[q];
+                for (int par = 0; par < 2; ++par) f.d[par][f.count] = batch_split_desc(sims[j], par);
+                f.lat[f.count] = j;
+                sblocks[j] = f.d[0][f.count].nblocks;
+                ++f.count;
+            }
+            if (f.count == 0 || (f.count < kSplitPerFill && q < k)) continue;
+            hipLaunchKernelGGL(k_fill_split, dim3(1), dim3(256), 0, st, f, sdesc);
+            const hipError_t e = hipGetLastError();
+            if (e != hipSuccess) return dev_err(e);
+            f.count = 0;
+        }
+        // block maps of the periodic and of the geometry lattices
+        for (int m = 0; m < 2; ++m) {
+            LatMap mp{};
+            for (int q = 0; q < k; ++q) {
+                const int j = order[q];
+                if ((sims[j]->g.mask != nullptr) != bool(m) || !split[m]) continue;
+                mp.lat[mp.n] = static_cast<unsigned char>(j);
+                mp.start[mp.n + 1] = mp.start[mp.n] + sblocks[j];
+                ++mp.n;
+            }
+            if (mp.n == 0) continue;
+            hipLaunchKernelGGL(k_fill_map, dim3(1), dim3(256), 0, st, mp, maps[m]);
+            const hipError_t e = hipGetLastError();
+            if (e != hipSuccess) return dev_err(e);
+        }
+    }
+
+    // sweep descriptors of every lattice, in chunks of kDescPerFill per launch
+    for (int first = 0; first < n && !(split[0] && split[1]); first += kDescPerFill) {
         DescFill f;
         f.first = first;
         f.count = std::min(kDescPerFill, n - first);
@@ -230,6 +311,7 @@ extern "C" int lbcg_batch_step_noalloc(lbcg_sim *const *sims, int32_t n, const i
     // block tables: each group lists its lattices in `order`, so the lattices
     // still running at a level are a prefix of it
     for (int masked = 0; masked < 2; ++masked) {
+        if (split[masked]) continue;
         TabFill t;
         t.n = 0;
         int tot = 0;
@@ -255,20 +337,29 @@ extern "C" int lbcg_batch_step_noalloc(lbcg_sim *const *sims, int32_t n, const i
     int a = k;
     while (a > 0) {
         const int64_t t1 = left[order[a - 1]];
-        int nbU = 0, nbM = 0;
-        for (int q = 0; q < a; ++q) (sims[order[q]]->g.mask ? nbM : nbU) += items[order[q]];
+        uint32_t nb[2] = {0, 0};
+        for (int q = 0; q < a; ++q) {
+            const int j = order[q], m = sims[j]->g.mask != nullptr;
+            nb[m] += split[m] ? sblocks[j] : uint32_t(items[j]);
+        }
         for (; t < t1; ++t) {
             const int par = int(t & 1);
+            const Desc *d = desc + size_t(par) * kMaxLat;
+            const SplitDesc *sd = sdesc + size_t(par) * kMaxLat;
             hipError_t e = hipSuccess;
-            if (compact) {
-                e = launch_step_compact_batch(s0->prec, desc + size_t(par) * kMaxLat, latU, itemU, nbU, st);
-            } else {
-                if (nbU > 0)
-                    e = launch_step_fused_batch(s0->prec, desc + size_t(par) * kMaxLat, latU, itemU, nbU, rows, false,
-                                                st);
-                if (e == hipSuccess && nbM > 0)
-                    e = launch_step_fused_batch(s0->prec, desc + size_t(par) * kMaxLat, latM, itemM, nbM, rows, true,
-                                                st);
+            if (nb[0] > 0) {
+                if (split[0])
+                    e = launch_step_psplit_batch(s0->prec, compact, sd, maps[0], nb[0], st);
+                else if (compact)
+                    e = launch_step_compact_batch(s0->prec, d, latU, itemU, int(nb[0]), st);
+                else
+                    e = launch_step_fused_batch(s0->prec, d, latU, itemU, int(nb[0]), rows, false, st);
+            }
+            if (e == hipSuccess && nb[1] > 0) {
+                if (split[1])
+                    e = launch_step_split_batch(s0->prec, sd, maps[1], nb[1], st);
+                else
+                    e = launch_step_fused_batch(s0->prec, d, latM, itemM, int(nb[1]), rows, true, st);
             }
             if (e != hipSuccess) return dev_err(e);
         }

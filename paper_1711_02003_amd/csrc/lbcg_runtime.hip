@@ -107,12 +107,12 @@ Plan make_plan(const lbcg_params *p) {
                                kAlign)
                     : 0;
     pl.psi = align_up(size_t(pl.pitch) * pl.tsize, kAlign);
-    // the split geometry step's moments: D3Q19 with a mask, F32 or F16,
+    // the split geometry step's scratch: D3Q19 with a mask, F32 or F16,
     // regularized collision
     pl.moms = p->mask && p->lattice == LBCG_D3Q19 && p->precision != LBCG_F64 && p->collision == LBCG_REGULARIZED &&
                       (p->kernel == LBCG_KERNEL_AUTO || p->kernel == LBCG_KERNEL_FUSED ||
                        p->kernel == LBCG_KERNEL_COMPACT)
-                  ? align_up(split_scratch_bytes(pl.pitch, p->dims[0], p->dims[1], p->dims[2]), kAlign)
+                  ? align_up(split_scratch_bytes(pl.pitch), kAlign)
                   : 0;
     pl.mask = p->mask ? align_up(size_t(pl.pitch), kAlign) : 0;
     pl.links = p->mask ? align_up(sizeof(uint32_t) * size_t(pl.pitch), kAlign) : 0;
@@ -158,7 +158,7 @@ hipError_t launch_fused(const lbcg_sim *s, const void *in, void *out, const uint
         return launch_step_psplit(s->prec, s->g, s->md, in, false, out, false, s->psi, nullptr, ctr_in, ctr_out,
                                   s->stream);
     if (shape.rows == 0)
-        return launch_step_split(s->prec, s->g, s->md, in, out, s->psi, s->moms, s->split, ctr_in, ctr_out,
+        return launch_step_split(s->prec, s->g, s->md, in, out, s->moms, s->split, ctr_in, ctr_out,
                                  s->stream);
     if (s->lattice == LBCG_D2Q9) return launch_step_tile2d(s->prec, s->g, s->md, in, out, ctr_in, ctr_out, s->stream);
     return launch_step_fused(s->prec, s->g, s->md, in, out, ctr_in, ctr_out, shape, s->stream);
@@ -248,9 +248,7 @@ FusedShape pick_shape(const lbcg_sim *s, const lbcg_params *p) {
         // With geometry, the split step when at most half the nodes are
         // fluid: the fluid then fills few column tiles, which the sweep can
         // spread over the device only in short z chunks.
-        int64_t fluid = 0;
-        for (int64_t n = 0; n < s->g.N; ++n) fluid += p->mask[n] == kFluid ? 1 : 0;
-        if (2 * fluid <= s->g.N) {
+        if (2 * s->fluid <= s->g.N) {
             sh.rows = 0;
             sh.zchunks = 1;
             return sh;
@@ -280,7 +278,7 @@ hipError_t enqueue_step(lbcg_sim *s, bool pulled) {
         const bool pair_in = !s->compact;
         hipError_t e =
             s->g.mask ? launch_step_cgeo(s->prec, s->g, s->md, pair_in, pair_in ? s->buf[s->cur] : s->cbuf[s->cur],
-                                         s->buf[s->cur], s->cbuf[s->cur ^ 1], s->buf[s->cur ^ 1], s->psi, s->moms,
+                                         s->buf[s->cur], s->cbuf[s->cur ^ 1], s->buf[s->cur ^ 1], s->moms,
                                          s->split, ctr_in, ctr_out, s->stream)
                       : launch_compact(s, pair_in ? s->buf[s->cur] : s->cbuf[s->cur], pair_in, s->cbuf[s->cur ^ 1],
                                        ctr_in, ctr_out, s->shape);
@@ -504,6 +502,9 @@ int lbcg_create(const lbcg_params *p, void *dev_buf, size_t bytes, void *hip_str
         s->stream = s->owned_stream;
     }
 
+    s->fluid = pl.N;
+    if (p->mask)
+        for (int64_t n = 0; n < pl.N; ++n) s->fluid -= p->mask[n] != kFluid ? 1 : 0;
     s->g.mask = s->mask_dev;
     s->g.inlets = s->in_dev;
     s->g.outlets = s->out_dev;

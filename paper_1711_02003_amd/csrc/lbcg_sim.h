@@ -21,7 +21,8 @@ struct lbcg_sim {
     int64_t step;
     void *psi;              // generic phase-field scratch (N values of the compute type)
     void *moms;             // split geometry step: its scratch (split_scratch_bytes), or null
-    lbcg::SplitPlan split;  // its block list lengths
+    int64_t fluid;          // fluid nodes
+    lbcg::SplitPlan split;  // its node list's length
     double *partials, *diag;
     uint32_t *ctr;          // time-step counter pair: ctr[cur] = steps taken since initialisation
     double *staging;        // field / population staging
@@ -44,3 +45,39 @@ struct lbcg_sim {
     bool graph_failed;
 };
 
+namespace lbcg {
+
+// Descriptor of a batched handle's step from buffer cur ^ par (0: its state)
+// into the other on the split step.
+inline SplitDesc batch_split_desc(const lbcg_sim *s, int par) {
+    const int a = s->cur ^ par, b = a ^ 1;
+    if (s->g.mask)
+        return split_desc(s->g, s->md, s->buf[a], s->buf[b], s->moms, s->split, s->ctr + a, s->ctr + b);
+    const bool cmp = s->kernel == LBCG_KERNEL_COMPACT;
+    // (a compact step's moments go to the pair buffer that holds no state)
+    return psplit_desc(s->g, s->md, cmp ? s->cbuf[a] : s->buf[a], cmp ? s->cbuf[b] : s->buf[b], cmp, s->psi,
+                       s->buf[b], s->ctr + a, s->ctr + b);
+}
+
+// Whether the batched split step applies to the handle.
+inline bool batch_split_ok(const lbcg_sim *s) {
+    return s->collision == LBCG_REGULARIZED && (s->g.mask ? s->moms != nullptr : psplit_supported(s->prec, s->g));
+}
+
+// Expected us per time level of the handle's share of a batched launch, on the
+// sweep (tiles of 64 x 8, z chunks of 32 planes, each with about three planes
+// of halo and start; with geometry the tiles in proportion to the fluid) and
+// on the split step, with the device full: the plane and node times of the
+// single-lattice steps, and with geometry 10.3 us per plane and 90 ps per
+// fluid node (FP16 8 us, 65 ps).
+inline void batch_cost(const lbcg_sim *s, double &sweep, double &split) {
+    const bool cmp = s->kernel == LBCG_KERNEL_COMPACT, half = s->prec == LBCG_F16, geo = s->g.mask != nullptr;
+    const double plane = geo ? (half ? 8.0 : 10.3) : (half ? (cmp ? 5.2 : 6.5) : (cmp ? 5.7 : 8.6));
+    const double node = geo ? (half ? 65e-6 : 90e-6) : (half ? (cmp ? 55e-6 : 54e-6) : (cmp ? 70e-6 : 80e-6));
+    const double tiles = double((s->g.nx + 63) / 64) * double((s->g.ny + 7) / 8);
+    const double planes = s->g.nz + 3.0 * ((s->g.nz + 31) / 32);
+    sweep = tiles * planes * plane / 256.0 * (double(s->fluid) / double(s->g.N));
+    split = double(s->fluid) * node;
+}
+
+}  // namespace lbcg

@@ -173,13 +173,18 @@ class Server:
         updates = 0.0
         while queue or running or inflight:
             now = self.clock() - t0
-            # admission in arrival order; stop at the first request that does not fit
+            # admission in arrival order; stop at the first request that does
+            # not fit.  An idle device starts on its first request at once:
+            # the next ones are set up while that request's slice runs.
+            idle = inflight is None and not running
             while queue and queue[0].arrival <= now:
                 if self.max_running and len(running) >= self.max_running:
                     break
                 if not self._admit(queue[0], now, running):
                     break
                 running.append(queue.pop(0))
+                if idle:
+                    break
             queued = None
             if running:
                 ids = tuple(r.id for r in running)
