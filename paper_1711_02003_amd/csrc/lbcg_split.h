@@ -105,8 +105,7 @@ struct MomHalves {
 };
 
 __device__ __forceinline__ void put_psi(float *psi, uint32_t pitch, uint32_t p, uint32_t zcol, float v) {
-    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), state_rsrc(psi, pitch * 4u), int(p * 4u), su(zcol * 4u),
-                                          0);
+    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), state_rsrc(psi, pitch * 4u), int(p * 4u), su(zcol * 4u), 0);
 }
 
 // The nodes around node (x, y, z), periodic.  With the plane uniform over the
