@@ -232,7 +232,10 @@ int lbcg_step(lbcg_sim *s, int64_t n);
  * Eq. (2), the phase field psi = (rho^R - rho^B)/(rho^R + rho^B) (N doubles
  * each) and the common velocity u of Eq. (3) (3N doubles, component-major).
  * Output pointers select the fields (NULL = skip).  Non-fluid nodes read 0.
- * Synchronizes. */
+ * Synchronizes.  Reads of 4 MiB and more, here and in lbcg_populations, go
+ * through 16 MiB of pinned host memory and up to 7 host threads that the
+ * library keeps per process while handles exist; one read at a time uses them,
+ * others at that moment take plain copies. */
 int lbcg_fields(lbcg_sim *s, double *rhoR, double *rhoB, double *u, double *psi);
 
 /* Pre-collision populations f_i^k of S_t (the distributions of Eq. (1)) in

@@ -567,6 +567,7 @@ int lbcg_create(const lbcg_params *p, void *dev_buf, size_t bytes, void *hip_str
     s->initialised = false;
     s->step = 0;
     s->graph_steps = kGraphSteps;
+    slots_use();
     *out = s;
     return LBCG_OK;
 }
@@ -657,21 +658,14 @@ int lbcg_fields(lbcg_sim *s, double *rhoR, double *rhoB, double *u, double *psi)
     if (!s) return LBCG_E_INVAL;
     if (!s->initialised) return LBCG_E_STATE;
     HIP_TRY(ensure_pairs(s));
-    const int64_t N = s->g.N, C = s->staging_nodes;
-    for (int64_t n0 = 0; n0 < N; n0 += C) {
-        const int64_t cnt = (N - n0) < C ? (N - n0) : C;
-        HIP_TRY(launch_fields(s->lattice, s->prec, s->g, s->md, s->buf[s->cur], s->pulled, n0, cnt, s->staging,
-                              s->stream));
-        const size_t b = sizeof(double) * size_t(cnt);
-        if (rhoR) HIP_TRY(hipMemcpyAsync(rhoR + n0, s->staging, b, hipMemcpyDeviceToHost, s->stream));
-        if (rhoB) HIP_TRY(hipMemcpyAsync(rhoB + n0, s->staging + cnt, b, hipMemcpyDeviceToHost, s->stream));
-        if (u)
-            for (int a = 0; a < 3; ++a)
-                HIP_TRY(hipMemcpyAsync(u + a * N + n0, s->staging + (2 + a) * cnt, b, hipMemcpyDeviceToHost,
-                                       s->stream));
-        if (psi) HIP_TRY(hipMemcpyAsync(psi + n0, s->staging + 5 * cnt, b, hipMemcpyDeviceToHost, s->stream));
-        HIP_TRY(hipStreamSynchronize(s->stream));
-    }
+    const int64_t N = s->g.N;
+    double *const dst[6] = {rhoR, rhoB, u, u ? u + N : nullptr, u ? u + 2 * N : nullptr, psi};
+    HIP_TRY(read_rows(
+        s,
+        [](lbcg_sim *h, int64_t n0, int64_t cnt, double *out) {
+            return launch_fields(h->lattice, h->prec, h->g, h->md, h->buf[h->cur], h->pulled, n0, cnt, out, h->stream);
+        },
+        6, dst));
     return LBCG_OK;
 }
 
@@ -679,16 +673,14 @@ int lbcg_populations(lbcg_sim *s, double *f) {
     if (!s || !f) return LBCG_E_INVAL;
     if (!s->initialised) return LBCG_E_STATE;
     HIP_TRY(ensure_pairs(s));
-    const int64_t N = s->g.N, C = s->staging_nodes;
-    for (int64_t n0 = 0; n0 < N; n0 += C) {
-        const int64_t cnt = (N - n0) < C ? (N - n0) : C;
-        HIP_TRY(launch_pops(s->lattice, s->prec, s->g, s->md, s->buf[s->cur], s->pulled, n0, cnt, s->staging,
-                            s->stream));
-        for (int c = 0; c < 2 * s->Q; ++c)
-            HIP_TRY(hipMemcpyAsync(f + int64_t(c) * N + n0, s->staging + int64_t(c) * cnt,
-                                   sizeof(double) * size_t(cnt), hipMemcpyDeviceToHost, s->stream));
-        HIP_TRY(hipStreamSynchronize(s->stream));
-    }
+    double *dst[2 * D3Q19::Q];
+    for (int c = 0; c < 2 * s->Q; ++c) dst[c] = f + int64_t(c) * s->g.N;
+    HIP_TRY(read_rows(
+        s,
+        [](lbcg_sim *h, int64_t n0, int64_t cnt, double *out) {
+            return launch_pops(h->lattice, h->prec, h->g, h->md, h->buf[h->cur], h->pulled, n0, cnt, out, h->stream);
+        },
+        2 * s->Q, dst));
     return LBCG_OK;
 }
 
@@ -947,6 +939,7 @@ void lbcg_destroy(lbcg_sim *s) {
     if (!s) return;
     (void)hipStreamSynchronize(s->stream);
     release(s);
+    slots_release();
     delete s;
 }
 

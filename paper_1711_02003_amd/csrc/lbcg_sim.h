@@ -47,6 +47,15 @@ struct lbcg_sim {
 
 namespace lbcg {
 
+// Reads `rows` values per node to the host (lbcg_readback.hip): `launch` queues
+// the values of nodes [n0, n0 + cnt) into device memory as rows of cnt
+// doubles; row r of all nodes goes to dst[r] (null: not read).  Synchronizes.
+typedef hipError_t (*RowsLaunch)(lbcg_sim *s, int64_t n0, int64_t cnt, double *out);
+hipError_t read_rows(lbcg_sim *s, RowsLaunch launch, int rows, double *const *dst);
+// A handle comes and goes: the read slots are freed with the last one.
+void slots_use();
+void slots_release();
+
 // Descriptor of a batched handle's step from buffer cur ^ par (0: its state)
 // into the other on the split step.
 inline SplitDesc batch_split_desc(const lbcg_sim *s, int par) {
