@@ -66,7 +66,7 @@ __global__ void __launch_bounds__(kBlock) k_psi(Geo g, Model<T> mo, const S *__r
     }
     int x, y, z;
     node_xyz(g, n, x, y, z);
-    Pops<L, T> p;
+    Pops<L, T, FlagBits<L::Q>> p;
     pull_node<L, S, T>(g, mo, st, x, y, z, n, pulled, p);
     T drho, rR, rB;
     densities<L, T>(p, drho, rR, rB);
@@ -121,13 +121,13 @@ __global__ void __launch_bounds__(kBlock) k_step_generic(Geo g, Model<T> mo, con
     if (code_at(g, n) != kFluid) return;
     int x, y, z;
     node_xyz(g, n, x, y, z);
-    Pops<L, T> p;
+    Pops<L, T, FlagBits<L::Q>> p;
     pull_node<L, S, T>(g, mo, in, x, y, z, n, pulled, p);
     Mom<T> m;
     moments<L, T>(p, m);
     T F[3];
     gradient<L, T>(g, psi, x, y, z, n, F);
-    PostOut<L, T> o;
+    PostOut<L, T, true> o;
     collide<L, T>(mo, m.drho, m.r36R, m.r36B, m.j, m.S, F, &p, o);
     typename PairOf<S>::type enc[L::Q];
     encode_out<L, S, T>(o, step, uint32_t(n), enc);
@@ -144,7 +144,7 @@ __global__ void __launch_bounds__(kBlock) k_fields(Geo g, Model<T> mo, const S *
     if (code_at(g, n) == kFluid) {
         int x, y, z;
         node_xyz(g, n, x, y, z);
-        Pops<L, T> p;
+        Pops<L, T, FlagBits<L::Q>> p;
         pull_node<L, S, T>(g, mo, st, x, y, z, n, pulled, p);
         Mom<T> m;
         moments<L, T>(p, m);
@@ -166,7 +166,7 @@ __global__ void __launch_bounds__(kBlock) k_pops(Geo g, Model<T> mo, const S *__
     const int64_t k = int64_t(blockIdx.x) * kBlock + threadIdx.x;
     if (k >= cnt) return;
     const int64_t n = n0 + k;
-    Pops<L, T> p;
+    Pops<L, T, FlagBits<L::Q>> p;
     const bool fl = code_at(g, n) == kFluid;
     if (fl) {
         int x, y, z;
@@ -205,7 +205,7 @@ __global__ void __launch_bounds__(kBlock) k_pops_at(Geo g, Model<T> mo, const S 
     }
     int x, y, z;
     node_xyz(g, n, x, y, z);
-    Pops<L, T> p;
+    Pops<L, T, FlagBits<L::Q>> p;
     pull_node<L, S, T>(g, mo, st, x, y, z, n, pulled, p);
 #pragma unroll
     for (int i = 0; i < L::Q; ++i) {
@@ -255,7 +255,7 @@ __global__ void __launch_bounds__(kBlock) k_diag(Geo g, Model<T> mo, const S *__
         if (code_at(g, n) != kFluid) continue;
         int x, y, z;
         node_xyz(g, n, x, y, z);
-        Pops<L, T> p;
+        Pops<L, T, FlagBits<L::Q>> p;
         pull_node<L, S, T>(g, mo, st, x, y, z, n, pulled, p);
         double r0 = 0.0, r1 = 0.0, jx = 0.0, jy = 0.0, jz = 0.0;
 #pragma unroll

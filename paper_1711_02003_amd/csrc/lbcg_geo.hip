@@ -313,13 +313,13 @@ __device__ __forceinline__ void geo_collide(const SplitDesc &a, uint32_t item) {
         OwnSum<L, S, float> sum;
 #pragma unroll
         for (int j = 0; j < L::Q; ++j)
-            sum.add(j, encode_step<L, S, float>(o.df[j], o.mm[j], (o.red >> j) & 1u, j, dz));
+            sum.add(j, encode_step<L, S, float>(o.df[j], o.mm[j], o.red(j), j, dz));
         io.om = sum.moments();
     }
     Dither dz(step, h.n);
 #pragma unroll
     for (int j = 0; j < L::Q; ++j) {
-        const P2 v = encode_step<L, S, float>(o.df[j], o.mm[j], (o.red >> j) & 1u, j, dz);
+        const P2 v = encode_step<L, S, float>(o.df[j], o.mm[j], o.red(j), j, dz);
         store_pair<P2>(rout, h.n * E, uint32_t(su(uint32_t(j) * a.pitch * E)), v);
         if (j == 0) continue;
         const int i = L::opp[j];
@@ -483,7 +483,6 @@ __global__ void __launch_bounds__(kGeoBlock) k_cgeo_moments(CGeoArgs ca) {
         // own total of the opposite direction and its own record, the
         // recolouring term with the opposite sign.  Links from inlets and
         // outlets are replaced below.
-        q.red = 0;
 #pragma unroll
         for (int i = 0; i < L::Q; ++i) {
             const bool wl = (wall >> i) & 1u;
@@ -495,7 +494,7 @@ __global__ void __launch_bounds__(kGeoBlock) k_cgeo_moments(CGeoArgs ca) {
             q.df[i] = d;
             q.mm[i] = r.M;
             q.vd[i] = wl ? -vd : vd;
-            q.red |= r.fl ? (1u << i) : 0u;
+            q.red.put(i, r.fl ? 1u : 0u);
         }
         if (io) {
             const __amdgpu_buffer_rsrc_t rg = state_rsrc(static_cast<const S *>(ca.gin), uint32_t(L::Q) * pitch * E);
@@ -503,11 +502,11 @@ __global__ void __launch_bounds__(kGeoBlock) k_cgeo_moments(CGeoArgs ca) {
             for (int i = 1; i < L::Q; ++i) {
                 if (!((io >> i) & 1u)) continue;
                 const P2 v = load_pair<P2>(rg, ar.vo(i) * E, uint32_t(su(uint32_t(i) * pitch * E)));
-                bool fl;
                 q.df[i] = Codec<S>::template df<L, T>(v.x, i);
-                q.mm[i] = Codec<S>::template col<T>(v.y, fl);
+                uint32_t word;
+                q.mm[i] = Codec<S>::template colw<T>(v.y, word);
+                q.red.put(i, word);
                 q.vd[i] = 0.0f;
-                q.red = fl ? (q.red | (1u << i)) : (q.red & ~(1u << i));
             }
         }
     }

@@ -151,7 +151,6 @@ __device__ __forceinline__ void pull_pairs(const void *in, uint32_t pitch, const
 #pragma unroll
     for (int i = 0; i < L::Q; ++i)
         v[i] = load_pair<P2>(r, ar.vo(i) * E, uint32_t(su((uint32_t(i) * pitch + ar.so(i)) * E)));
-    q.red = 0;
 #pragma unroll
     for (int i = 0; i < L::Q; ++i) decode_pair<L, S, float>(v[i], i, q);
 }
@@ -180,7 +179,6 @@ __device__ __forceinline__ void pull_compact(const void *in, uint32_t pitch, con
     typedef CStore<S> St;
     const uint32_t base = uint32_t(L::Q) * pitch * St::E;
     const __amdgpu_buffer_rsrc_t r = state_rsrc(static_cast<const uint8_t *>(in), base + pitch * (St::kRecA + St::kRecB));
-    q.red = 0;
 #pragma unroll
     for (int i = 0; i < L::Q; ++i) {
         const uint32_t c = ar.vo(i), z = ar.so(i);
@@ -188,11 +186,11 @@ __device__ __forceinline__ void pull_compact(const void *in, uint32_t pitch, con
         const typename St::RawA ra = St::load_a(r, c * St::kRecA, base + z * St::kRecA);
         const typename St::RawB rb = St::load_b(r, c * St::kRecB, base + pitch * St::kRecA + z * St::kRecB);
         const f4 e = St::entry(ra, rb);
-        bool fl;
         q.df[i] = St::df(d, i);
-        q.mm[i] = Codec<float>::col<float>(e[0], fl);
+        uint32_t word;
+        q.mm[i] = Codec<float>::colw<float>(e[0], word);
+        q.red.put(i, word);
         q.vd[i] = rec_term(i, e, St::ratio(rb));
-        q.red |= fl ? (1u << i) : 0u;
     }
 }
 

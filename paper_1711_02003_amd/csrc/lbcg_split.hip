@@ -106,7 +106,7 @@ __device__ __forceinline__ void p_collide(const SplitDesc &a, uint32_t item) {
 #pragma unroll
         for (int i = 0; i < L::Q; ++i)
             store_pair<P2>(rout, h.p * E, uint32_t(su((uint32_t(i) * a.pitch + ar.zp[1]) * E)),
-                           encode_step<L, S, float>(o.df[i], o.mm[i], (o.red >> i) & 1u, i, dz));
+                           encode_step<L, S, float>(o.df[i], o.mm[i], o.red(i), i, dz));
     }
 }
 

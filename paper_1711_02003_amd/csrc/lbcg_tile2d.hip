@@ -187,7 +187,6 @@ struct Raw2d {
             v[i] = tload<P2>(r, c.from(D2Q9::cx[i], D2Q9::cy[i]) * E, uint32_t(i) * pitch * E);
     }
     __device__ __forceinline__ void take(Pops<D2Q9, T> &q) const {
-        q.red = 0;
 #pragma unroll
         for (int i = 0; i < D2Q9::Q; ++i) decode_pair<D2Q9, S, T>(v[i], i, q);
     }
@@ -338,7 +337,7 @@ __global__ void __launch_bounds__(NT) k_tile2d(Tile2dArgs a, Model<T> mo) {
         Dither dz(step, n);
 #pragma unroll
         for (int i = 0; i < L::Q; ++i) {
-            const P2 v = encode_step<L, S, T>(o.df[i], o.mm[i], (o.red >> i) & 1u, i, dz);
+            const P2 v = encode_step<L, S, T>(o.df[i], o.mm[i], o.red(i), i, dz);
             tstore<P2>(rout, n * E, uint32_t(i) * a.pitch * E, v);
             if (MASKED) enc[i] = v;
         }
@@ -368,15 +367,14 @@ __global__ void __launch_bounds__(NT) k_tile2d(Tile2dArgs a, Model<T> mo) {
 template <int W>
 __device__ __forceinline__ void split_tile(const float d[D2Q9::Q], const tf4 *rec, int c, CPops<D2Q9, float> &p) {
     using L = D2Q9;
-    p.red = 0;
 #pragma unroll
     for (int i = 0; i < L::Q; ++i) {
         const int cx = L::cx[i], cy = L::cy[i];
         const tf4 s = rec[c - cy * W - cx];
-        bool fl;
         p.df[i] = d[i];
-        p.mm[i] = Codec<float>::col<float>(s[0], fl);
-        p.red |= fl ? (1u << i) : 0u;
+        uint32_t word;
+        p.mm[i] = Codec<float>::colw<float>(s[0], word);
+        p.red.put(i, word);
         const int n2 = cx * cx + cy * cy;
         if (n2 == 0) {
             p.vd[i] = 0.0f;
