@@ -218,16 +218,19 @@ bool split_allowed(const lbcg_sim *s) {
 
 // Whether the split step of a periodic D3Q19 lattice is expected to be faster
 // than the sweep of shape sh: the sweep's plane iterations at the time one
-// takes with every CU busy (256^3: 131 of them), against the split step's
-// time per node plus its two launches.  Per state and storage, measured:
-// plane 8.6 / 5.7 / 6.5 / 5.2 us (pair FP32, compact FP32, pair FP16, compact
-// FP16), node 80 / 70 / 54 / 55 ps.
+// takes with every CU busy (the compact sweep's on lattices that do not yet
+// fill the memory too: only those are near the line), against the split
+// step's time per node plus its two launches.  Per state and storage: plane
+// 8.6 / 4.9 / 6.5 / 4.7 us (pair FP32, compact FP32, pair FP16, compact FP16),
+// node 80 / 66 / 54 / 53 ps.  Sweep against split, measured: 128^3 pairs FP32 152
+// / 153 us, 210 x 150 x 131 398 / 339 (FP16 316 / 221), compact 96^3 58 / 62 (FP16
+// 57 / 46), 64^3 22 / 20 (21 / 17), 210 x 150 x 131 FP16 233 / 251.
 bool split_faster(const lbcg_sim *s, const FusedShape &sh) {
     const bool cmp = s->kernel == LBCG_KERNEL_COMPACT, half = s->prec == LBCG_F16;
-    const double plane_us = half ? (cmp ? 5.2 : 6.5) : (cmp ? 5.7 : 8.6);
-    const double node_us = half ? (cmp ? 55e-6 : 54e-6) : (cmp ? 70e-6 : 80e-6);
+    const double plane_us = half ? (cmp ? 4.7 : 6.5) : (cmp ? 4.9 : 8.6);
+    const double node_us = half ? (cmp ? 53e-6 : 54e-6) : (cmp ? 66e-6 : 80e-6);
     const double sweep = double(sweep_planes(s, sh, resident_blocks(s, sh), sh.zchunks)) * plane_us;
-    return 8.0 + double(s->g.N) * node_us < sweep;
+    return 6.0 + double(s->g.N) * node_us < sweep;
 }
 
 FusedShape pick_shape(const lbcg_sim *s, const lbcg_params *p) {
@@ -910,13 +913,20 @@ int lbcg_tune(lbcg_sim *s, int32_t *rows, int32_t *zchunks) {
                 if (best_ms[ci] == 0 || ms < best_ms[ci]) best_ms[ci] = ms;
             }
         }
+        // The compact split step is timed too fast here, where every launch
+        // reads one unchanged state (128^3 FP16 it was picked at 105 us a step
+        // over the sweep's 90, 128 x 100 x 90 FP32 at 77 over 66): where the
+        // rule expects the sweep to be faster it has to win by a fifth.
         FusedShape pick = s->shape;
         float best = 0;
-        for (size_t ci = 0; ci < cand.size() && e == hipSuccess; ++ci)
-            if (best == 0 || best_ms[ci] < best) {
-                best = best_ms[ci];
+        for (size_t ci = 0; ci < cand.size() && e == hipSuccess; ++ci) {
+            const bool doubted = cmp && cand[ci].split && !split_faster(s, cand[ci]);
+            const float ms = best_ms[ci] * (doubted ? 1.2f : 1.0f);
+            if (best == 0 || ms < best) {
+                best = ms;
                 pick = cand[ci];
             }
+        }
         (void)hipEventDestroy(e0);
         (void)hipEventDestroy(e1);
         if (e != hipSuccess) return dev_err(e);

@@ -81,8 +81,8 @@ inline bool batch_split_ok(const lbcg_sim *s) {
 // fluid node (FP16 8 us, 65 ps).
 inline void batch_cost(const lbcg_sim *s, double &sweep, double &split) {
     const bool cmp = s->kernel == LBCG_KERNEL_COMPACT, half = s->prec == LBCG_F16, geo = s->g.mask != nullptr;
-    const double plane = geo ? (half ? 8.0 : 10.3) : (half ? (cmp ? 5.2 : 6.5) : (cmp ? 5.7 : 8.6));
-    const double node = geo ? (half ? 65e-6 : 90e-6) : (half ? (cmp ? 55e-6 : 54e-6) : (cmp ? 70e-6 : 80e-6));
+    const double plane = geo ? (half ? 8.0 : 10.3) : (half ? (cmp ? 4.7 : 6.5) : (cmp ? 4.9 : 8.6));
+    const double node = geo ? (half ? 65e-6 : 90e-6) : (half ? (cmp ? 53e-6 : 54e-6) : (cmp ? 66e-6 : 80e-6));
     const double tiles = double((s->g.nx + 63) / 64) * double((s->g.ny + 7) / 8);
     const double planes = s->g.nz + 3.0 * ((s->g.nz + 31) / 32);
     sweep = tiles * planes * plane / 256.0 * (double(s->fluid) / double(s->g.N));
