@@ -411,12 +411,12 @@ struct Pops {
 // is 36 x its recolouring term c_i . V (V of the sender's speed class, signed
 // for the sender's minority colour), so that 36 x the minority colour part is
 // mm[i] (36 w_i + 36 df[i]) + vd[i].
-template <class L, typename T>
+template <class L, typename T, class F = FlagMasks<L::Q>>
 struct CPops {
     T df[L::Q];
     T mm[L::Q];
     T vd[L::Q];
-    FlagMasks<L::Q> red;
+    F red;
 };
 
 // The two stored values of a population travel together: the state is Q
@@ -543,8 +543,8 @@ __device__ __forceinline__ void colour_parts(const Pops<L, T, F> &p, int i, T &r
     r36 = p.red.pick(i, t, mu);
     b36 = p.red.pick(i, mu, t);
 }
-template <class L, typename T>
-__device__ __forceinline__ void colour_parts(const CPops<L, T> &p, int i, T &r36, T &b36) {
+template <class L, typename T, class F>
+__device__ __forceinline__ void colour_parts(const CPops<L, T, F> &p, int i, T &r36, T &b36) {
     const T d = p.df[i];
     const T mu = p.mm[i] * (T(w36<L>(i)) + T(36) * d) + p.vd[i];
     const T t = T(36) * d - mu;

@@ -173,8 +173,9 @@ __device__ __forceinline__ float rec_term(int i, const f4 e, float Rd) {
 
 // The 19 totals that a node pulls, each split with its sender's record (from
 // the cache: a record serves 19 receivers).
-template <typename S, bool UZ>
-__device__ __forceinline__ void pull_compact(const void *in, uint32_t pitch, const Around<UZ> &ar, CPops<D3Q19, float> &q) {
+template <typename S, bool UZ, class F>
+__device__ __forceinline__ void pull_compact(const void *in, uint32_t pitch, const Around<UZ> &ar,
+                                             CPops<D3Q19, float, F> &q) {
     using L = D3Q19;
     typedef CStore<S> St;
     const uint32_t base = uint32_t(L::Q) * pitch * St::E;
