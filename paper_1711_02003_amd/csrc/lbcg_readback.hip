@@ -114,7 +114,12 @@ struct Pool {
         }
     }
     bool open() {
-        if (hipHostMalloc(reinterpret_cast<void **>(&mem), 2 * kSlotBytes, hipHostMallocPortable) != hipSuccess) {
+        // (relaxed: an allocation must not end a capture of another thread)
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+        (void)hipThreadExchangeStreamCaptureMode(&mode);
+        const hipError_t e = hipHostMalloc(reinterpret_cast<void **>(&mem), 2 * kSlotBytes, hipHostMallocPortable);
+        (void)hipThreadExchangeStreamCaptureMode(&mode);
+        if (e != hipSuccess) {
             (void)hipGetLastError();
             mem = nullptr;
             return false;
