@@ -103,6 +103,16 @@ extern "C" {
 #define LBCG_KERNEL_FUSED 2
 #define LBCG_KERNEL_COMPACT 3
 
+/* Forms of the time step: the kernels that a handle's steps run after its
+ * first step, which is always the two passes.  Where a handle can take more
+ * than one form, they give bitwise the same states. */
+#define LBCG_FORM_AUTO 0     /* the library's choice */
+#define LBCG_FORM_SWEEP 1    /* D3Q19: the column sweep, one kernel */
+#define LBCG_FORM_SPLIT 2    /* D3Q19: the split step, a thread per node: one
+                                kernel for the moments, one for the collision */
+#define LBCG_FORM_TILE 3     /* D2Q9: the tile step, one kernel */
+#define LBCG_FORM_TWO_PASS 4 /* the generic kernel: the phase field, then the step */
+
 /* Mask codes (one byte per node): 0 fluid; 1 neutral wall (half-way
  * bounce-back; the colour gradient sees the fluid node's own phase value
  * there); 2 + j inlet j, j < 62 (moving-wall velocity inlet); 64 + j wetting
@@ -287,8 +297,11 @@ const char *lbcg_strerror(int status);
  * width (64; or 32 on the compact D3Q19 sweep).  A periodic D3Q19 lattice
  * whose launch shape is automatic may be stepped by a pair of kernels with one
  * thread per node instead of the sweep, bitwise the same, where that is faster
- * (lattices that fill the device only in part); the sweep's shape that it
- * stands for is reported.  rows 0 on the fused kernel:
+ * (lattices that fill the device only in part); the shape reported is then the
+ * one the sweep would have, and lbcg_step_form says which of the two runs.  A
+ * handle made with a given shape (tile) runs the sweep; to carry a choice over
+ * to other handles give them the shape and, with lbcg_set_step_form, the form.
+ * rows 0 on the fused kernel:
  * the split step of a D3Q19 lattice with geometry (one kernel pulls and
  * writes every fluid node's psi and collision moments, a second forms the
  * gradient, collides and stores, inlet and outlet values included; bitwise
@@ -296,6 +309,20 @@ const char *lbcg_strerror(int status);
  * chunk halo, which dominate where the fluid fills few tiles).
  * NULL outputs are skipped. */
 int lbcg_launch_info(lbcg_sim *s, int32_t *kernel, int32_t *rows, int32_t *zchunks, int32_t *tile_width);
+
+/* The form of the time step that the handle's steps run after the first (one
+ * of LBCG_FORM_SWEEP, _SPLIT, _TILE, _TWO_PASS). */
+int lbcg_step_form(lbcg_sim *s, int32_t *form);
+
+/* Choose the form of the handle's later steps: LBCG_FORM_SWEEP or
+ * LBCG_FORM_SPLIT on a D3Q19 lattice of the fused or the compact kernel that
+ * can take it, or LBCG_FORM_AUTO for the choice of lbcg_create or of the last
+ * lbcg_tune.  LBCG_E_INVAL, with nothing changed, if the handle cannot take
+ * the form (the split step: regularized collision; the sweep: not the compact
+ * state with geometry); the form it already runs is always accepted.
+ * lbcg_tune keeps to a form chosen here, and lbcg_batch_step_noalloc takes it
+ * into account. */
+int lbcg_set_step_form(lbcg_sim *s, int32_t form);
 
 /* Choose the fused (or compact) kernel's launch shape for this handle by
  * timing candidate shapes on the handle's own lattice (D3Q19: rows 4 or 8,
@@ -305,7 +332,9 @@ int lbcg_launch_info(lbcg_sim *s, int32_t *kernel, int32_t *rows, int32_t *zchun
  * planes), stepping the current state
  * into the spare buffer so the state does not change (the compact kernel is
  * timed on a compact state also before the handle's first compact step).  Keeps
- * the fastest shape for later steps and reports it.  No effect on the
+ * the fastest for later steps and reports its shape, or, if that is the
+ * two-kernel step of a periodic lattice, the fastest sweep's (lbcg_step_form
+ * tells).  No effect on the
  * generic kernel and on D2Q9, whose step has one launch shape.  Synchronizes. */
 int lbcg_tune(lbcg_sim *s, int32_t *rows, int32_t *zchunks);
 

@@ -268,6 +268,58 @@ FusedShape pick_shape(const lbcg_sim *s, const lbcg_params *p) {
     return sh;
 }
 
+// Whether the handle's pulled steps run the D2Q9 tile step.
+bool on_tiles(const lbcg_sim *s) {
+    if (s->lattice != LBCG_D2Q9) return false;
+    if (s->kernel == LBCG_KERNEL_FUSED || s->kernel == LBCG_KERNEL_COMPACT) return true;
+    // FP64 D2Q9: the tile step too, the two-pass kernel's expressions in one
+    // launch (64 x 64: 9.2 -> 5.0 us per step)
+    return s->prec == LBCG_F64 && tile2d_supported(s->prec, s->g);
+}
+
+// Form of the handle's pulled steps in launch shape sh.
+int form_of(const lbcg_sim *s, const FusedShape &sh) {
+    if (on_tiles(s)) return LBCG_FORM_TILE;
+    if (s->kernel == LBCG_KERNEL_GENERIC) return LBCG_FORM_TWO_PASS;
+    return sh.split || sh.rows == 0 ? LBCG_FORM_SPLIT : LBCG_FORM_SWEEP;
+}
+
+// The launch shape sh in the given form (false: the handle cannot take it).
+bool shape_in_form(const lbcg_sim *s, int form, FusedShape &sh) {
+    if (form_of(s, sh) == form) return true;
+    if (s->lattice != LBCG_D3Q19 || s->kernel == LBCG_KERNEL_GENERIC) return false;
+    if (form == LBCG_FORM_SPLIT) {
+        if (s->g.mask) {
+            if (!s->moms) return false;
+            sh = FusedShape{0, 1, 64};
+        } else {
+            if (!split_allowed(s)) return false;
+            sh.split = true;
+        }
+        return true;
+    }
+    if (form != LBCG_FORM_SWEEP || (s->kernel == LBCG_KERNEL_COMPACT && s->g.mask)) return false;
+    if (sh.rows == 0) {
+        sh = FusedShape{8, 1, 64};
+        sh.zchunks = int(best_zchunks(s, sh, resident_blocks(s, sh)));
+    }
+    sh.split = false;
+    return true;
+}
+
+// Launch shape of later steps; the graphs replay the shape they were captured
+// with.
+void use_shape(lbcg_sim *s, const FusedShape &sh) {
+    if (sh.rows == s->shape.rows && sh.zchunks == s->shape.zchunks && sh.tx == s->shape.tx && sh.split == s->shape.split)
+        return;
+    for (int k = 0; k < 2; ++k)
+        if (s->graph[k]) {
+            (void)hipGraphExecDestroy(s->graph[k]);
+            s->graph[k] = nullptr;
+        }
+    s->shape = sh;
+}
+
 // One time step from buf[cur] into buf[cur ^ 1].
 // With the compact kernel, a pulled step reads cbuf[cur] (or, right after an
 // initialisation or a restore, the pair state in buf[cur]) and writes
@@ -292,9 +344,7 @@ hipError_t enqueue_step(lbcg_sim *s, bool pulled) {
         return e;
     }
     if (s->kernel == LBCG_KERNEL_FUSED && pulled) return launch_fused(s, in, out, ctr_in, ctr_out, s->shape);
-    // FP64 D2Q9: the tile step too, the two-pass kernel's expressions in one
-    // launch (64 x 64: 9.2 -> 5.0 us per step)
-    if (pulled && s->prec == LBCG_F64 && s->lattice == LBCG_D2Q9 && tile2d_supported(s->prec, s->g))
+    if (pulled && on_tiles(s))
         return launch_step_tile2d(s->prec, s->g, s->md, in, out, ctr_in, ctr_out, s->stream);
     hipError_t e = launch_psi(s->lattice, s->prec, s->g, s->md, in, pulled, s->psi, s->stream);
     if (e != hipSuccess) return e;
@@ -562,7 +612,8 @@ int lbcg_create(const lbcg_params *p, void *dev_buf, size_t bytes, void *hip_str
         return LBCG_E_INVAL;
     }
     s->kernel = kind;
-    s->shape = pick_shape(s, p);
+    s->shape = s->own_shape = pick_shape(s, p);
+    s->form = LBCG_FORM_AUTO;
     s->cur = 0;
     s->compact = false;
     s->expanded = false;
@@ -813,6 +864,21 @@ int lbcg_launch_info(lbcg_sim *s, int32_t *kernel, int32_t *rows, int32_t *zchun
     return LBCG_OK;
 }
 
+int lbcg_step_form(lbcg_sim *s, int32_t *form) {
+    if (!s || !form) return LBCG_E_INVAL;
+    *form = form_of(s, s->shape);
+    return LBCG_OK;
+}
+
+int lbcg_set_step_form(lbcg_sim *s, int32_t form) {
+    if (!s) return LBCG_E_INVAL;
+    FusedShape sh = s->own_shape;
+    if (form != LBCG_FORM_AUTO && !shape_in_form(s, form, sh)) return LBCG_E_INVAL;
+    s->form = form == LBCG_FORM_SWEEP || form == LBCG_FORM_SPLIT ? form : LBCG_FORM_AUTO;
+    use_shape(s, sh);
+    return LBCG_OK;
+}
+
 int lbcg_tune(lbcg_sim *s, int32_t *rows, int32_t *zchunks) {
     if (!s) return LBCG_E_INVAL;
     if (!s->initialised) return LBCG_E_STATE;
@@ -854,8 +920,7 @@ int lbcg_tune(lbcg_sim *s, int32_t *rows, int32_t *zchunks) {
                 if (!seen) cand.push_back(FusedShape{r, zc, tx});
             }
         }
-        // periodic lattices: the split step, reported with the sweep shape that
-        // it replaces
+        // periodic lattices: the split step
         if (split_allowed(s)) {
             FusedShape c{8, 1, 64};
             c.zchunks = int(best_zchunks(s, c, resident_blocks(s, c)));
@@ -917,28 +982,31 @@ int lbcg_tune(lbcg_sim *s, int32_t *rows, int32_t *zchunks) {
         // reads one unchanged state (128^3 FP16 it was picked at 105 us a step
         // over the sweep's 90, 128 x 100 x 90 FP32 at 77 over 66): where the
         // rule expects the sweep to be faster it has to win by a fifth.
-        FusedShape pick = s->shape;
-        float best = 0;
+        FusedShape pick = s->shape, sweep = s->shape;
+        float best = 0, best_sweep = 0;
         for (size_t ci = 0; ci < cand.size() && e == hipSuccess; ++ci) {
             const bool doubted = cmp && cand[ci].split && !split_faster(s, cand[ci]);
             const float ms = best_ms[ci] * (doubted ? 1.2f : 1.0f);
+            if (form_of(s, cand[ci]) == LBCG_FORM_SWEEP && (best_sweep == 0 || ms < best_sweep)) {
+                best_sweep = ms;
+                sweep = cand[ci];
+            }
+            if (s->form != LBCG_FORM_AUTO && form_of(s, cand[ci]) != s->form) continue;
             if (best == 0 || ms < best) {
                 best = ms;
                 pick = cand[ci];
             }
         }
+        // a periodic lattice on the split step reports the fastest sweep
+        if (pick.split) {
+            pick = sweep;
+            pick.split = true;
+        }
         (void)hipEventDestroy(e0);
         (void)hipEventDestroy(e1);
         if (e != hipSuccess) return dev_err(e);
-        if (pick.rows != s->shape.rows || pick.zchunks != s->shape.zchunks || pick.tx != s->shape.tx ||
-            pick.split != s->shape.split) {
-            for (int k = 0; k < 2; ++k)
-                if (s->graph[k]) {
-                    (void)hipGraphExecDestroy(s->graph[k]);
-                    s->graph[k] = nullptr;
-                }
-            s->shape = pick;
-        }
+        s->own_shape = pick;
+        use_shape(s, pick);
     }
     if (rows) *rows = s->shape.rows;
     if (zchunks) *zchunks = s->shape.zchunks;

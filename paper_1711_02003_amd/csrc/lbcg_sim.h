@@ -12,6 +12,8 @@ struct lbcg_sim {
     lbcg::Geo g;
     lbcg::ModelD md;
     lbcg::FusedShape shape;
+    lbcg::FusedShape own_shape;  // chosen by lbcg_create or lbcg_tune (shape: also by lbcg_set_step_form)
+    int form;               // LBCG_FORM_SWEEP or _SPLIT if lbcg_set_step_form chose it, else LBCG_FORM_AUTO
     size_t elem;            // bytes per stored value
     size_t state_bytes;     // one state buffer
     void *buf[2];

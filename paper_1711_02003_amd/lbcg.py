@@ -24,6 +24,7 @@ F64, F32, F16 = 0, 1, 2
 REGULARIZED, BGK, BGK_COLOUR = 0, 1, 2
 INLET0, WALL0, OUTLET0 = 2, 64, 128  # mask codes: inlet j, wetting wall j, outlet j
 KERNEL_AUTO, KERNEL_GENERIC, KERNEL_FUSED, KERNEL_COMPACT = 0, 1, 2, 3
+FORM_AUTO, FORM_SWEEP, FORM_SPLIT, FORM_TILE, FORM_TWO_PASS = 0, 1, 2, 3, 4
 PRECISIONS = {"f64": F64, "f32": F32, "f16": F16}
 LATTICES = {"D2Q9": D2Q9, "D3Q19": D3Q19}
 
@@ -88,6 +89,8 @@ _SIGS = {
     "lbcg_destroy": (None, [C.c_void_p]),
     "lbcg_strerror": (C.c_char_p, [C.c_int]),
     "lbcg_launch_info": (C.c_int, [C.c_void_p, _P(C.c_int32), _P(C.c_int32), _P(C.c_int32), _P(C.c_int32)]),
+    "lbcg_step_form": (C.c_int, [C.c_void_p, _P(C.c_int32)]),
+    "lbcg_set_step_form": (C.c_int, [C.c_void_p, C.c_int32]),
     "lbcg_tune": (C.c_int, [C.c_void_p, _P(C.c_int32), _P(C.c_int32)]),
     "lbcg_batch_create": (C.c_int, [_P(C.c_void_p), C.c_int32, _P(C.c_int32), _P(C.c_void_p)]),
     "lbcg_batch_step": (C.c_int, [C.c_void_p, _P(C.c_int64)]),
@@ -335,13 +338,24 @@ class Sim:
         k, r, z, t = C.c_int32(), C.c_int32(), C.c_int32(), C.c_int32()
         _check(self._lib.lbcg_launch_info(self._handle(), C.byref(k), C.byref(r), C.byref(z), C.byref(t)),
                "lbcg_launch_info")
-        return {"kernel": k.value, "rows": r.value, "zchunks": z.value, "tile_width": t.value}
+        return {"kernel": k.value, "rows": r.value, "zchunks": z.value, "tile_width": t.value, "form": self.step_form()}
+
+    def step_form(self) -> int:
+        """FORM_SWEEP, FORM_SPLIT, FORM_TILE or FORM_TWO_PASS: what the steps after the first run."""
+        f = C.c_int32()
+        _check(self._lib.lbcg_step_form(self._handle(), C.byref(f)), "lbcg_step_form")
+        return f.value
+
+    def set_step_form(self, form: int):
+        _check(self._lib.lbcg_set_step_form(self._handle(), int(form)), "lbcg_set_step_form")
+        return self
 
     def tune(self):
         """Time candidate launch shapes of the fused kernel and keep the fastest."""
         r, z = C.c_int32(), C.c_int32()
         _check(self._lib.lbcg_tune(self._handle(), C.byref(r), C.byref(z)), "lbcg_tune")
-        return {"rows": r.value, "zchunks": z.value, "tile_width": self.launch_info()["tile_width"]}
+        i = self.launch_info()
+        return {"rows": r.value, "zchunks": z.value, "tile_width": i["tile_width"], "form": i["form"]}
 
     def close(self):
         if self._h is not None:
