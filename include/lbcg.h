@@ -70,7 +70,10 @@ extern "C" {
 /* Kernel choice: automatic, the two-pass generic kernel (every lattice,
  * precision, collision and boundary) or the fused single-pass kernel (F32 or
  * F16 storage, state buffers below 4 GiB; D3Q19 or D2Q9, any collision
- * form, any geometry).  Automatic picks the fused kernel where it applies.
+ * form, any geometry).  Automatic picks the fused kernel where it applies;
+ * on D2Q9 with F64 storage (state buffers below 4 GiB) it is reported as the
+ * generic kernel and steps, after the first step, on the D2Q9 tile step, the
+ * same expressions in one pass (lbcg_step_form tells).
  *
  * LBCG_KERNEL_COMPACT (never picked automatically): the fused sweeps on a
  * compact state, regularized collision: for periodic lattices D3Q19 with F32

@@ -272,9 +272,10 @@ FusedShape pick_shape(const lbcg_sim *s, const lbcg_params *p) {
 bool on_tiles(const lbcg_sim *s) {
     if (s->lattice != LBCG_D2Q9) return false;
     if (s->kernel == LBCG_KERNEL_FUSED || s->kernel == LBCG_KERNEL_COMPACT) return true;
-    // FP64 D2Q9: the tile step too, the two-pass kernel's expressions in one
-    // launch (64 x 64: 9.2 -> 5.0 us per step)
-    return s->prec == LBCG_F64 && tile2d_supported(s->prec, s->g);
+    // FP64 D2Q9 on the automatic choice: the tile step too, the two-pass
+    // kernel's expressions in one launch (64 x 64: 9.2 -> 5.0 us per step); a
+    // caller that asks for the generic kernel gets its two passes
+    return s->auto_kernel && s->prec == LBCG_F64 && tile2d_supported(s->prec, s->g);
 }
 
 // Form of the handle's pulled steps in launch shape sh.
@@ -612,6 +613,7 @@ int lbcg_create(const lbcg_params *p, void *dev_buf, size_t bytes, void *hip_str
         return LBCG_E_INVAL;
     }
     s->kernel = kind;
+    s->auto_kernel = p->kernel == LBCG_KERNEL_AUTO;
     s->shape = s->own_shape = pick_shape(s, p);
     s->form = LBCG_FORM_AUTO;
     s->cur = 0;

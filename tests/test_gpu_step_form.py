@@ -93,3 +93,21 @@ def test_forms_that_a_handle_cannot_take_are_refused(L):  # noqa: F811
             assert e.value.status == L.E_INVAL
             assert s.step_form() == form
         assert s.set_step_form(form).step_form() == form
+
+
+@pytest.mark.parametrize("masked", [False, True])
+@pytest.mark.parametrize("coll", ["REGULARIZED", "BGK", "BGK_COLOUR"])
+@pytest.mark.parametrize("dims", [(33, 9), (65, 17), (200, 130)])
+def test_f64_d2q9_tiles_match_the_two_passes_bitwise(L, dims, coll, masked):  # noqa: F811
+    # the automatic choice steps on tiles; a caller that asks for the generic
+    # kernel gets the two passes, and both the same bits
+    from tests.test_gpu_tile2d import _random
+    w = _random(dims, seed=sum(dims), masked=masked)
+    fl = slice(None) if w.mask is None else w.mask == 0
+    a = L.Sim.from_workload(w, precision="f64", collision=getattr(L, coll))
+    g = L.Sim.from_workload(w, precision="f64", collision=getattr(L, coll), kernel=L.KERNEL_GENERIC)
+    assert a.launch_info()["kernel"] == g.launch_info()["kernel"] == L.KERNEL_GENERIC
+    assert a.step_form() == L.FORM_TILE and g.step_form() == L.FORM_TWO_PASS
+    for n in (1, 2, 35):
+        p, q = (s.step(n).populations()[..., fl] for s in (a, g))
+        assert np.isfinite(p).all() and np.array_equal(p, q), (dims, coll, masked, n)
