@@ -322,9 +322,9 @@ int lbcg_step_form(lbcg_sim *s, int32_t *form);
  * can take it, or LBCG_FORM_AUTO for the choice of lbcg_create or of the last
  * lbcg_tune.  LBCG_E_INVAL, with nothing changed, if the handle cannot take
  * the form (the split step: regularized collision; the sweep: not the compact
- * state with geometry); the form it already runs is always accepted.
- * lbcg_tune keeps to a form chosen here, and lbcg_batch_step_noalloc takes it
- * into account. */
+ * state with geometry); the form it already runs is always accepted.  A change
+ * waits for the handle's queued work.  lbcg_tune keeps to a form chosen here,
+ * and lbcg_batch_step_noalloc takes it into account. */
 int lbcg_set_step_form(lbcg_sim *s, int32_t form);
 
 /* Choose the fused (or compact) kernel's launch shape for this handle by
@@ -369,6 +369,17 @@ int lbcg_batch_step(lbcg_batch *b, const int64_t *nsteps);
 /* Launch shape of the batch: rows per block, z planes per chunk, total blocks
  * of one level over all lattices. */
 int lbcg_batch_launch_info(lbcg_batch *b, int32_t *rows, int32_t *zplanes, int64_t *blocks);
+/* The forms of the time step (LBCG_FORM_SWEEP or _SPLIT) that lbcg_batch_step
+ * takes for the periodic lattices (form[0]) and for those with geometry
+ * (form[1]); LBCG_FORM_AUTO where the batch has none of them.  Set: a given
+ * form, or LBCG_FORM_AUTO for the choice of lbcg_batch_create.  A batch made
+ * with a given tile takes the sweeps; a timed choice is carried over to
+ * another batch by giving it the tile that lbcg_batch_launch_info reports and,
+ * with lbcg_batch_set_step_form, the forms.  LBCG_E_INVAL, with nothing
+ * changed, for the split step in a batch of more than 256 handles.  A change
+ * waits for the batch's queued work. */
+int lbcg_batch_step_form(lbcg_batch *b, int32_t form[2]);
+int lbcg_batch_set_step_form(lbcg_batch *b, const int32_t form[2]);
 /* Waits for the batch's queued work, then releases its tables. */
 void lbcg_batch_destroy(lbcg_batch *b);
 
@@ -379,10 +390,15 @@ void lbcg_batch_destroy(lbcg_batch *b);
  * nsteps[j] >= 0 steps (n entries) with the launch shape tile = {rows per
  * block (4 or 8; 8 on the compact kernel), z planes per chunk (>= 1)}; the
  * requirements on the handles are those of lbcg_batch_create, and all must
- * belong to the device current at the call.  Periodic or geometry lattices
- * step on the split steps instead where that is expected to be faster (narrow
- * or mostly solid lattices).  Results per lattice are bitwise those of
- * lbcg_batch_step and lbcg_step.
+ * belong to the device current at the call.  The periodic lattices, and those
+ * with geometry, step on the split steps instead of the sweep where that is
+ * expected to be faster than the sweep in the given shape (narrow or mostly
+ * solid lattices, few blocks).  Handles with a form of their own
+ * (lbcg_set_step_form) decide for their group: the sweep if one of them has
+ * LBCG_FORM_SWEEP, else the split step if all have LBCG_FORM_SPLIT.
+ * lbcg_batch_noalloc_form reports the forms, as lbcg_batch_step_form does, that
+ * a call with these handles, all of them stepping, takes.  Results per lattice
+ * are bitwise those of lbcg_batch_step and lbcg_step.
  * The descriptors and block tables live in one fixed area of device memory
  * that the library holds per device until the process ends (about 1.2 MB),
  * written by small kernels queued on the handles' stream: at most
@@ -396,6 +412,7 @@ void lbcg_batch_destroy(lbcg_batch *b);
 #define LBCG_NOALLOC_MAX_LATTICES 256
 #define LBCG_NOALLOC_MAX_BLOCKS 65536
 int lbcg_batch_step_noalloc(lbcg_sim *const *sims, int32_t n, const int32_t *tile, const int64_t *nsteps);
+int lbcg_batch_noalloc_form(lbcg_sim *const *sims, int32_t n, const int32_t *tile, int32_t form[2]);
 
 #ifdef __cplusplus
 }

@@ -65,6 +65,9 @@ struct lbcg_batch {
     int prec = 0;
     bool compact = false;  // every lattice on the compact-state kernel
     bool split[2] = {false, false};  // periodic / geometry lattices on the split steps
+    bool own_split[2] = {false, false};  // as chosen at creation
+    bool can_split[2] = {false, false};
+    int members[2] = {0, 0};  // periodic / geometry lattices
     int rows = 8, zplanes = 32;
     hipStream_t stream = nullptr;
     std::vector<int> zchunks, items;  // per lattice, for the current shape
@@ -400,14 +403,11 @@ int lbcg_batch_create(lbcg_sim *const *sims, int32_t n, const int32_t *tile, lbc
         return LBCG_E_INVAL;
     }
     b->bytes = 2 * size_t(n) * sizeof(Desc) + 2 * sizeof(int) * size_t(b->capU + b->capM);
-    // the split steps are candidates of a timed batch
-    bool can_split[2] = {tuned && n <= kBatchLatMax, tuned && n <= kBatchLatMax};
-    int members[2] = {0, 0};
-    for (int j = 0; j < n; ++j) {
-        ++members[is_masked(sims[j])];
-        if (!batch_split_ok(sims[j])) can_split[is_masked(sims[j])] = false;
-    }
-    if (can_split[0] || can_split[1]) {
+    for (int j = 0; j < n; ++j) ++b->members[is_masked(sims[j])];
+    for (int m = 0; m < 2; ++m) b->can_split[m] = b->members[m] && n <= kBatchLatMax;
+    for (int j = 0; j < n; ++j)
+        if (!batch_split_ok(sims[j])) b->can_split[is_masked(sims[j])] = false;
+    if (b->can_split[0] || b->can_split[1]) {
         b->sofs = (b->bytes + 255) / 256 * 256;
         b->bytes = b->sofs + 2 * size_t(n) * sizeof(SplitDesc) + 2 * sizeof(LatMap);
     }
@@ -436,8 +436,9 @@ int lbcg_batch_create(lbcg_sim *const *sims, int32_t n, const int32_t *tile, lbc
             }
         }
         set_shape(b, pick.first, pick.second);
+        // the split steps are candidates too
         for (int m = 0; m < 2; ++m) {
-            if (!can_split[m] || !members[m]) continue;
+            if (!b->can_split[m]) continue;
             b->split[m] = true;
             float ms = 0;
             const int rc = time_shape(b, &ms);
@@ -449,6 +450,7 @@ int lbcg_batch_create(lbcg_sim *const *sims, int32_t n, const int32_t *tile, lbc
                 best = ms;
             else
                 b->split[m] = false;
+            b->own_split[m] = b->split[m];
         }
     } else {
         set_shape(b, tile[0], tile[1]);
@@ -523,6 +525,30 @@ int lbcg_batch_launch_info(lbcg_batch *b, int32_t *rows, int32_t *zplanes, int64
         for (int v : b->items) t += v;
         *blocks = t;
     }
+    return LBCG_OK;
+}
+
+int lbcg_batch_step_form(lbcg_batch *b, int32_t form[2]) {
+    if (!b || !form) return LBCG_E_INVAL;
+    for (int m = 0; m < 2; ++m)
+        form[m] = !b->members[m] ? LBCG_FORM_AUTO : (b->split[m] ? LBCG_FORM_SPLIT : LBCG_FORM_SWEEP);
+    return LBCG_OK;
+}
+
+int lbcg_batch_set_step_form(lbcg_batch *b, const int32_t form[2]) {
+    if (!b || !form) return LBCG_E_INVAL;
+    bool split[2];
+    for (int m = 0; m < 2; ++m) {
+        if (form[m] != LBCG_FORM_AUTO && form[m] != LBCG_FORM_SWEEP && form[m] != LBCG_FORM_SPLIT) return LBCG_E_INVAL;
+        if (form[m] == LBCG_FORM_SPLIT && b->members[m] && !b->can_split[m]) return LBCG_E_INVAL;
+        split[m] = form[m] == LBCG_FORM_AUTO ? b->own_split[m] : form[m] == LBCG_FORM_SPLIT && b->members[m];
+    }
+    if (split[0] == b->split[0] && split[1] == b->split[1]) return LBCG_OK;
+    if (!b->graphs.empty()) {  // they replay the forms they were captured with
+        HIP_TRY(hipStreamSynchronize(b->stream));
+        drop_graphs(b);
+    }
+    for (int m = 0; m < 2; ++m) b->split[m] = split[m];
     return LBCG_OK;
 }
 

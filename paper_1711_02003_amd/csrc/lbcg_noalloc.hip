@@ -148,11 +148,10 @@ int chunks_for(const lbcg_sim *s, int zplanes) {
     return int(z < 1 ? 1 : (z > 4096 ? 4096 : z));
 }
 
-}  // namespace
-
-extern "C" int lbcg_batch_step_noalloc(lbcg_sim *const *sims, int32_t n, const int32_t *tile,
-                                       const int64_t *nsteps) {
-    if (!sims || !tile || !nsteps || n < 1) return LBCG_E_INVAL;
+// Requirements on the handles and the launch shape, and each lattice's z chunks
+// and work items in it.
+int check_call(lbcg_sim *const *sims, int32_t n, const int32_t *tile, int zch[kMaxLat], int items[kMaxLat]) {
+    if (!sims || !tile || n < 1) return LBCG_E_INVAL;
     if (n > kMaxLat) return LBCG_E_INVAL;
     const int rows = tile[0], zplanes = tile[1];
     if ((rows != 4 && rows != 8) || zplanes < 1) return LBCG_E_INVAL;
@@ -167,34 +166,81 @@ extern "C" int lbcg_batch_step_noalloc(lbcg_sim *const *sims, int32_t n, const i
         if (s->kernel == LBCG_KERNEL_COMPACT && s->g.mask) return LBCG_E_INVAL;
         if (s->kernel != s0->kernel || s->prec != s0->prec || s->stream != s0->stream || s->device != s0->device)
             return LBCG_E_INVAL;
-        if (nsteps[j] < 0) return LBCG_E_INVAL;
         for (int k = 0; k < j; ++k)
             if (sims[k] == s) return LBCG_E_INVAL;
     }
-    const bool compact = s0->kernel == LBCG_KERNEL_COMPACT;
-    if (compact && rows != 8) return LBCG_E_INVAL;  // the compact sweep has 8-row tiles
+    if (s0->kernel == LBCG_KERNEL_COMPACT && rows != 8) return LBCG_E_INVAL;  // the compact sweep has 8-row tiles
     int dev = -1;
     if (hipGetDevice(&dev) != hipSuccess) {
         (void)hipGetLastError();
         return LBCG_E_DEVICE;
     }
     if (dev != s0->device) return LBCG_E_INVAL;
-
-    // work items per lattice and the size of each group's table (fixed-size
-    // arrays: the call allocates nothing, host memory included)
-    int zch[kMaxLat], items[kMaxLat];
-    int64_t totU = 0, totM = 0;
+    int64_t total[2] = {0, 0};
     for (int j = 0; j < n; ++j) {
         const lbcg_sim *s = sims[j];
         zch[j] = chunks_for(s, zplanes);
         const int64_t it = int64_t((s->g.nx + kTileX - 1) / kTileX) * ((s->g.ny + rows - 1) / rows) * zch[j];
         if (it > kMaxBlocks) return LBCG_E_INVAL;
         items[j] = int(it);
-        (s->g.mask ? totM : totU) += it;
+        total[s->g.mask != nullptr] += it;
     }
-    if (totU > kMaxBlocks || totM > kMaxBlocks) return LBCG_E_INVAL;
+    return total[0] > kMaxBlocks || total[1] > kMaxBlocks ? LBCG_E_INVAL : LBCG_OK;
+}
+
+// Each group of the listed lattices (periodic, geometry) on the sweep or, where
+// every member can take it and it is expected to be faster, on the split step;
+// the forms chosen for the handles themselves come first.
+void choose_split(lbcg_sim *const *sims, const int *list, int k, bool split[2]) {
+    split[0] = split[1] = true;
+    bool all[2] = {true, true}, none[2] = {false, false};  // handles set to the split step, to the sweep
+    double sweep_us[2] = {0, 0}, split_us[2] = {0, 0};
+    for (int q = 0; q < k; ++q) {
+        const lbcg_sim *s = sims[list[q]];
+        const int m = s->g.mask != nullptr;
+        split[m] = split[m] && batch_split_ok(s);
+        all[m] = all[m] && s->form == LBCG_FORM_SPLIT;
+        none[m] = none[m] || s->form == LBCG_FORM_SWEEP;
+        double a = 0, b = 0;
+        batch_cost(s, a, b);
+        sweep_us[m] += a;
+        split_us[m] += b;
+    }
+    for (int m = 0; m < 2; ++m) split[m] = split[m] && !none[m] && (all[m] || split_us[m] < sweep_us[m]);
+}
+
+}  // namespace
+
+extern "C" int lbcg_batch_noalloc_form(lbcg_sim *const *sims, int32_t n, const int32_t *tile, int32_t form[2]) {
+    if (!form) return LBCG_E_INVAL;
+    int zch[kMaxLat], items[kMaxLat], list[kMaxLat];
+    const int rc = check_call(sims, n, tile, zch, items);
+    if (rc) return rc;
+    bool members[2] = {false, false}, split[2];
+    for (int j = 0; j < n; ++j) {
+        list[j] = j;
+        members[sims[j]->g.mask != nullptr] = true;
+    }
+    choose_split(sims, list, n, split);
+    for (int m = 0; m < 2; ++m) form[m] = !members[m] ? LBCG_FORM_AUTO : (split[m] ? LBCG_FORM_SPLIT : LBCG_FORM_SWEEP);
+    return LBCG_OK;
+}
+
+extern "C" int lbcg_batch_step_noalloc(lbcg_sim *const *sims, int32_t n, const int32_t *tile,
+                                       const int64_t *nsteps) {
+    if (!nsteps) return LBCG_E_INVAL;
+    // work items per lattice (fixed-size arrays: the call allocates nothing,
+    // host memory included)
+    int zch[kMaxLat], items[kMaxLat];
+    int rc = check_call(sims, n, tile, zch, items);
+    if (rc) return rc;
+    for (int j = 0; j < n; ++j)
+        if (nsteps[j] < 0) return LBCG_E_INVAL;
+    const lbcg_sim *s0 = sims[0];
+    const int rows = tile[0], dev = s0->device;
+    const bool compact = s0->kernel == LBCG_KERNEL_COMPACT;
     unsigned char *area = nullptr;
-    int rc = area_of_device(dev, &area);
+    rc = area_of_device(dev, &area);
     if (rc) return rc;
     Desc *desc = reinterpret_cast<Desc *>(area);
     int *latU = reinterpret_cast<int *>(area + kDescBytes), *itemU = latU + kMaxBlocks;
@@ -234,20 +280,8 @@ extern "C" int lbcg_batch_step_noalloc(lbcg_sim *const *sims, int32_t n, const i
     }
     const hipStream_t st = s0->stream;
 
-    // Each group (periodic, geometry) on the sweep or, where every member can
-    // take it and it is expected to be faster, on the split step.
-    bool split[2] = {true, true};
-    double sweep_us[2] = {0, 0}, split_us[2] = {0, 0};
-    for (int q = 0; q < k; ++q) {
-        const lbcg_sim *s = sims[order[q]];
-        const int m = s->g.mask != nullptr;
-        split[m] = split[m] && batch_split_ok(s);
-        double a = 0, b = 0;
-        batch_cost(s, a, b);
-        sweep_us[m] += a;
-        split_us[m] += b;
-    }
-    for (int m = 0; m < 2; ++m) split[m] = split[m] && split_us[m] < sweep_us[m];
+    bool split[2];
+    choose_split(sims, order, k, split);
     SplitDesc *sdesc = reinterpret_cast<SplitDesc *>(area + kDescBytes + kTabBytes);
     LatMap *maps[2];
     for (int m = 0; m < 2; ++m)

@@ -308,17 +308,20 @@ bool shape_in_form(const lbcg_sim *s, int form, FusedShape &sh) {
     return true;
 }
 
-// Launch shape of later steps; the graphs replay the shape they were captured
-// with.
-void use_shape(lbcg_sim *s, const FusedShape &sh) {
+// Launch shape of later steps.  The graphs replay the shape they were captured
+// with, and go once they have run.
+hipError_t use_shape(lbcg_sim *s, const FusedShape &sh) {
     if (sh.rows == s->shape.rows && sh.zchunks == s->shape.zchunks && sh.tx == s->shape.tx && sh.split == s->shape.split)
-        return;
+        return hipSuccess;
     for (int k = 0; k < 2; ++k)
         if (s->graph[k]) {
+            const hipError_t e = hipStreamSynchronize(s->stream);
+            if (e != hipSuccess) return e;
             (void)hipGraphExecDestroy(s->graph[k]);
             s->graph[k] = nullptr;
         }
     s->shape = sh;
+    return hipSuccess;
 }
 
 // One time step from buf[cur] into buf[cur ^ 1].
@@ -876,8 +879,8 @@ int lbcg_set_step_form(lbcg_sim *s, int32_t form) {
     if (!s) return LBCG_E_INVAL;
     FusedShape sh = s->own_shape;
     if (form != LBCG_FORM_AUTO && !shape_in_form(s, form, sh)) return LBCG_E_INVAL;
+    HIP_TRY(use_shape(s, sh));
     s->form = form == LBCG_FORM_SWEEP || form == LBCG_FORM_SPLIT ? form : LBCG_FORM_AUTO;
-    use_shape(s, sh);
     return LBCG_OK;
 }
 
@@ -1007,8 +1010,8 @@ int lbcg_tune(lbcg_sim *s, int32_t *rows, int32_t *zchunks) {
         (void)hipEventDestroy(e0);
         (void)hipEventDestroy(e1);
         if (e != hipSuccess) return dev_err(e);
+        HIP_TRY(use_shape(s, pick));
         s->own_shape = pick;
-        use_shape(s, pick);
     }
     if (rows) *rows = s->shape.rows;
     if (zchunks) *zchunks = s->shape.zchunks;

@@ -95,8 +95,11 @@ _SIGS = {
     "lbcg_batch_create": (C.c_int, [_P(C.c_void_p), C.c_int32, _P(C.c_int32), _P(C.c_void_p)]),
     "lbcg_batch_step": (C.c_int, [C.c_void_p, _P(C.c_int64)]),
     "lbcg_batch_launch_info": (C.c_int, [C.c_void_p, _P(C.c_int32), _P(C.c_int32), _P(C.c_int64)]),
+    "lbcg_batch_step_form": (C.c_int, [C.c_void_p, _P(C.c_int32)]),
+    "lbcg_batch_set_step_form": (C.c_int, [C.c_void_p, _P(C.c_int32)]),
     "lbcg_batch_destroy": (None, [C.c_void_p]),
     "lbcg_batch_step_noalloc": (C.c_int, [_P(C.c_void_p), C.c_int32, _P(C.c_int32), _P(C.c_int64)]),
+    "lbcg_batch_noalloc_form": (C.c_int, [_P(C.c_void_p), C.c_int32, _P(C.c_int32), _P(C.c_int32)]),
 }
 NOALLOC_MAX_LATTICES, NOALLOC_MAX_BLOCKS = 256, 65536
 
@@ -405,7 +408,18 @@ class Batch:
         r, z, b = C.c_int32(), C.c_int32(), C.c_int64()
         _check(self._lib.lbcg_batch_launch_info(self._h, C.byref(r), C.byref(z), C.byref(b)),
                "lbcg_batch_launch_info")
-        return {"rows": r.value, "zplanes": z.value, "blocks": b.value}
+        return {"rows": r.value, "zplanes": z.value, "blocks": b.value, "forms": self.step_form()}
+
+    def step_form(self) -> tuple:
+        """Forms of the periodic and of the geometry lattices (FORM_AUTO: none of them)."""
+        f = (C.c_int32 * 2)()
+        _check(self._lib.lbcg_batch_step_form(self._h, f), "lbcg_batch_step_form")
+        return tuple(f)
+
+    def set_step_form(self, periodic: int = FORM_AUTO, geometry: int = FORM_AUTO):
+        f = (C.c_int32 * 2)(int(periodic), int(geometry))
+        _check(self._lib.lbcg_batch_set_step_form(self._h, f), "lbcg_batch_set_step_form")
+        return self
 
     def close(self):
         if self._h is not None:
@@ -433,3 +447,13 @@ def batch_step_noalloc(sims, nsteps, tile):
     t = (C.c_int32 * 2)(*[int(v) for v in tile])
     _check(lib.lbcg_batch_step_noalloc(arr, len(sims), t, n.ctypes.data_as(C.POINTER(C.c_int64))),
            "lbcg_batch_step_noalloc")
+
+
+def batch_noalloc_form(sims, tile) -> tuple:
+    """Forms that batch_step_noalloc takes for the periodic and for the
+    geometry lattices among sims (FORM_AUTO: none of them)."""
+    sims = list(sims)
+    arr = (C.c_void_p * len(sims))(*[s._handle().value for s in sims])
+    t, f = (C.c_int32 * 2)(*[int(v) for v in tile]), (C.c_int32 * 2)()
+    _check(load_library().lbcg_batch_noalloc_form(arr, len(sims), t, f), "lbcg_batch_noalloc_form")
+    return tuple(f)
