@@ -189,24 +189,23 @@ int check_call(lbcg_sim *const *sims, int32_t n, const int32_t *tile, int zch[kM
 }
 
 // Each group of the listed lattices (periodic, geometry) on the sweep or, where
-// every member can take it and it is expected to be faster, on the split step;
-// the forms chosen for the handles themselves come first.
-void choose_split(lbcg_sim *const *sims, const int *list, int k, bool split[2]) {
+// every member can take it and it is expected to be faster than the sweep in the
+// given shape (GroupCost), on the split step; the forms chosen for the handles
+// themselves come first.
+void choose_split(lbcg_sim *const *sims, const int *list, int k, int rows, const int *zch, bool split[2]) {
     split[0] = split[1] = true;
     bool all[2] = {true, true}, none[2] = {false, false};  // handles set to the split step, to the sweep
-    double sweep_us[2] = {0, 0}, split_us[2] = {0, 0};
+    GroupCost cost[2];
     for (int q = 0; q < k; ++q) {
         const lbcg_sim *s = sims[list[q]];
         const int m = s->g.mask != nullptr;
         split[m] = split[m] && batch_split_ok(s);
         all[m] = all[m] && s->form == LBCG_FORM_SPLIT;
         none[m] = none[m] || s->form == LBCG_FORM_SWEEP;
-        double a = 0, b = 0;
-        batch_cost(s, a, b);
-        sweep_us[m] += a;
-        split_us[m] += b;
+        cost[m].add(s, rows, zch[list[q]]);
     }
-    for (int m = 0; m < 2; ++m) split[m] = split[m] && !none[m] && (all[m] || split_us[m] < sweep_us[m]);
+    for (int m = 0; m < 2; ++m)
+        split[m] = split[m] && cost[m].first && !none[m] && (all[m] || cost[m].split_us() < cost[m].sweep_us());
 }
 
 }  // namespace
@@ -221,7 +220,7 @@ extern "C" int lbcg_batch_noalloc_form(lbcg_sim *const *sims, int32_t n, const i
         list[j] = j;
         members[sims[j]->g.mask != nullptr] = true;
     }
-    choose_split(sims, list, n, split);
+    choose_split(sims, list, n, tile[0], zch, split);
     for (int m = 0; m < 2; ++m) form[m] = !members[m] ? LBCG_FORM_AUTO : (split[m] ? LBCG_FORM_SPLIT : LBCG_FORM_SWEEP);
     return LBCG_OK;
 }
@@ -281,7 +280,7 @@ extern "C" int lbcg_batch_step_noalloc(lbcg_sim *const *sims, int32_t n, const i
     const hipStream_t st = s0->stream;
 
     bool split[2];
-    choose_split(sims, order, k, split);
+    choose_split(sims, order, k, rows, zch, split);
     SplitDesc *sdesc = reinterpret_cast<SplitDesc *>(area + kDescBytes + kTabBytes);
     LatMap *maps[2];
     for (int m = 0; m < 2; ++m)

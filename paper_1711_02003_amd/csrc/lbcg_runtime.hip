@@ -226,11 +226,9 @@ bool split_allowed(const lbcg_sim *s) {
 // / 153 us, 210 x 150 x 131 398 / 339 (FP16 316 / 221), compact 96^3 58 / 62 (FP16
 // 57 / 46), 64^3 22 / 20 (21 / 17), 210 x 150 x 131 FP16 233 / 251.
 bool split_faster(const lbcg_sim *s, const FusedShape &sh) {
-    const bool cmp = s->kernel == LBCG_KERNEL_COMPACT, half = s->prec == LBCG_F16;
-    const double plane_us = half ? (cmp ? 4.7 : 6.5) : (cmp ? 4.9 : 8.6);
-    const double node_us = half ? (cmp ? 53e-6 : 54e-6) : (cmp ? 66e-6 : 80e-6);
-    const double sweep = double(sweep_planes(s, sh, resident_blocks(s, sh), sh.zchunks)) * plane_us;
-    return 6.0 + double(s->g.N) * node_us < sweep;
+    const StepCost c = step_cost(s);
+    const double sweep = double(sweep_planes(s, sh, resident_blocks(s, sh), sh.zchunks)) * c.plane;
+    return 6.0 + double(s->g.N) * 1e-6 * c.node < sweep;
 }
 
 FusedShape pick_shape(const lbcg_sim *s, const lbcg_params *p) {
@@ -617,6 +615,11 @@ int lbcg_create(const lbcg_params *p, void *dev_buf, size_t bytes, void *hip_str
     }
     s->kernel = kind;
     s->auto_kernel = p->kernel == LBCG_KERNEL_AUTO;
+    s->resident[0] = s->resident[1] = 1;
+    if (s->lattice == LBCG_D3Q19 && kind != LBCG_KERNEL_GENERIC && s->collision == LBCG_REGULARIZED)
+        for (int rows : {4, 8})
+            if (kind == LBCG_KERNEL_FUSED || rows == 8)
+                s->resident[rows == 8] = int(resident_blocks(s, FusedShape{rows, 1, 64}));
     s->shape = s->own_shape = pick_shape(s, p);
     s->form = LBCG_FORM_AUTO;
     s->cur = 0;

@@ -25,6 +25,7 @@ struct lbcg_sim {
     void *psi;              // generic phase-field scratch (N values of the compute type)
     void *moms;             // split geometry step: its scratch (split_scratch_bytes), or null
     int64_t fluid;          // fluid nodes
+    int resident[2];        // blocks of the batched D3Q19 sweep that the device holds: tiles of 4, of 8 rows
     lbcg::SplitPlan split;  // its node list's length
     double *partials, *diag;
     uint32_t *ctr;          // time-step counter pair: ctr[cur] = steps taken since initialisation
@@ -76,20 +77,61 @@ inline bool batch_split_ok(const lbcg_sim *s) {
     return s->collision == LBCG_REGULARIZED && (s->g.mask ? s->moms != nullptr : psplit_supported(s->prec, s->g));
 }
 
-// Expected us per time level of the handle's share of a batched launch, on the
-// sweep (tiles of 64 x 8, z chunks of 32 planes, each with about three planes
-// of halo and start; with geometry the tiles in proportion to the fluid) and
-// on the split step, with the device full: the plane and node times of the
-// single-lattice steps, and with geometry 10.3 us per plane and 90 ps per
-// fluid node (FP16 8 us, 65 ps).
-inline void batch_cost(const lbcg_sim *s, double &sweep, double &split) {
-    const bool cmp = s->kernel == LBCG_KERNEL_COMPACT, half = s->prec == LBCG_F16, geo = s->g.mask != nullptr;
-    const double plane = geo ? (half ? 8.0 : 10.3) : (half ? (cmp ? 4.7 : 6.5) : (cmp ? 4.9 : 8.6));
-    const double node = geo ? (half ? 65e-6 : 90e-6) : (half ? (cmp ? 53e-6 : 54e-6) : (cmp ? 66e-6 : 80e-6));
-    const double tiles = double((s->g.nx + 63) / 64) * double((s->g.ny + 7) / 8);
-    const double planes = s->g.nz + 3.0 * ((s->g.nz + 31) / 32);
-    sweep = tiles * planes * plane / 256.0 * (double(s->fluid) / double(s->g.N));
-    split = double(s->fluid) * node;
+// Times that the choices between a D3Q19 sweep and the split step are made by:
+// us per plane iteration of a 64 x 8 sweep block with every CU busy, ps per
+// fluid node of a single lattice's split step, and of a batched split launch,
+// whose rate falls from `small` to `large` as its nodes grow from `from` to `to`
+// million (the states no longer stay in the cache).  Batched split step, us
+// measured: one 96^3 pairs FP32 58 (FP16 48), compact 65 (48); 128^3 143 (101),
+// 151 (107); 256 x 128 x 128 336 (208), 316 (221); 64 boxes of 17.6 M nodes 1569
+// (1025), 1541 (1180); four channels of 1.95 M fluid nodes 209 (159).
+struct StepCost {
+    double plane, node, small, large, from, to;
+};
+inline StepCost step_cost(const lbcg_sim *s) {
+    const bool half = s->prec == LBCG_F16;
+    if (s->g.mask) return half ? StepCost{12.9, 76, 76, 76, 1, 2} : StepCost{11.7, 98, 98, 98, 1, 2};
+    if (s->kernel == LBCG_KERNEL_COMPACT)
+        return half ? StepCost{4.7, 53, 46, 68, 2, 8} : StepCost{4.9, 66, 66, 88, 2, 8};
+    return half ? StepCost{6.5, 54, 47, 58, 2, 8} : StepCost{8.6, 80, 65, 90, 2, 4};
 }
+
+// Expected us of one level of a group of lattices (all periodic or all with
+// geometry) on the batched sweep in a given launch shape and on the batched split
+// step.  The sweep's blocks run on `resident` places; each takes its planes and
+// about three more.  Blocks of one length run in rounds; of mixed lengths, the
+// places share the work, and the last of them wait for half a block on average.
+// With geometry a tile counts in proportion to the fluid.  Sweep against split,
+// measured (allocation-free step): 128^3 compact FP32 in chunks of 16 planes
+// 112 / 151, of 64 320 / 151; 16 boxes of 3.7 M nodes FP32 pairs in chunks of 8
+// planes 384 / 316; two junctions of 0.17 M fluid nodes 94 to 381 / 28.
+struct GroupCost {
+    const lbcg_sim *first = nullptr;
+    double work = 0, items = 0, longest = 0, nodes = 0, resident = 1;
+    void add(const lbcg_sim *s, int rows, int64_t zchunks) {
+        const double part = double(s->fluid) / double(s->g.N);
+        const double tiles = double((s->g.nx + 63) / 64) * double((s->g.ny + rows - 1) / rows) * part;
+        const double planes = double((s->g.nz + zchunks - 1) / zchunks + 3);
+        work += tiles * double(s->g.nz + 3 * zchunks);
+        items += tiles * double(zchunks);
+        if (planes > longest) longest = planes;
+        nodes += double(s->fluid);
+        if (!first) {
+            first = s;
+            resident = s->resident[rows == 8];
+        }
+    }
+    double sweep_us() const {
+        const double rounds = double(int64_t((items + resident - 1) / resident)) * longest;
+        const double shared = work / resident + 0.5 * longest;
+        return (rounds < shared ? rounds : shared) * step_cost(first).plane;
+    }
+    double split_us() const {
+        const StepCost c = step_cost(first);
+        double a = (nodes * 1e-6 - c.from) / (c.to - c.from);
+        a = a < 0 ? 0 : (a > 1 ? 1 : a);
+        return 6.0 + nodes * 1e-6 * (c.small + (c.large - c.small) * a);
+    }
+};
 
 }  // namespace lbcg

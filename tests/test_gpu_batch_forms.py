@@ -122,3 +122,21 @@ def test_refused_forms(L):  # noqa: F811
         L.batch_noalloc_form(sims[:2], (6, 4))
     for s in sims:
         s.close()
+
+
+def test_noalloc_weighs_the_given_shape(L):  # noqa: F811
+    # Groups where the faster form is several times faster or depends on the
+    # given launch shape: 128^3 lattices sweep well in chunks of 16 planes (112
+    # us against 151) and badly in chunks of 64 (320 against 151), junctions on
+    # sweeps take 94 to 381 us against 28.
+    from paper_1711_02003_amd import workloads as W
+    for kern, w, tile, form in [("COMPACT", W.static_droplet_3d(n=128, R=20.0), (8, 16), "SWEEP"),
+                                ("COMPACT", W.static_droplet_3d(n=128, R=20.0), (8, 64), "SPLIT"),
+                                ("FUSED", W.static_droplet_3d(n=128, R=20.0), (8, 64), "SPLIT"),
+                                ("FUSED", W.flow_focusing(128, 48, 14), (8, 32), "SPLIT"),
+                                ("FUSED", _box((20, 17, 13), 1), (4, 4), "SPLIT")]:
+        s = L.Sim.from_workload(w, kernel=getattr(L, "KERNEL_" + kern))
+        got = L.batch_noalloc_form([s], tile)[0 if w.mask is None else 1]
+        print(kern, w.dims, tile, got, flush=True)
+        assert got == getattr(L, "FORM_" + form), (kern, w.dims, tile)
+        s.close()
