@@ -446,6 +446,15 @@ int lbcg_batch_create(lbcg_sim *const *sims, int32_t n, const int32_t *tile, lbc
                 destroy(b);
                 return rc;
             }
+            // The compact split step is timed too fast here, where every level
+            // reads one unchanged state (one 128^3 lattice FP16 was given it at
+            // 108 us a level over the sweep's 93, four of 128 x 128 x 12 FP32 at
+            // 61 over 48): where the sweep is expected to be faster it has to win
+            // by a fifth.
+            GroupCost cost;
+            for (int j = 0; j < n; ++j)
+                if (is_masked(sims[j]) == bool(m)) cost.add(sims[j], b->rows, b->zchunks[size_t(j)]);
+            if (b->compact && cost.sweep_us() <= cost.split_us()) ms *= 1.2f;
             if (ms < best)
                 best = ms;
             else

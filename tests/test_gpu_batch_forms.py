@@ -140,3 +140,13 @@ def test_noalloc_weighs_the_given_shape(L):  # noqa: F811
         print(kern, w.dims, tile, got, flush=True)
         assert got == getattr(L, "FORM_" + form), (kern, w.dims, tile)
         s.close()
+
+
+def test_timed_compact_batch_keeps_the_faster_form(L):  # noqa: F811
+    # one 128^3 lattice, FP16 compact: the sweep takes 93 us a level, the split
+    # step 107, and 20 % less than that when a level is timed on a fixed state
+    from paper_1711_02003_amd import workloads as W
+    s = L.Sim.from_workload(W.static_droplet_3d(n=128, R=20.0), precision="f16", kernel=L.KERNEL_COMPACT).step(2)
+    b = L.Batch([s])
+    assert b.step_form() == (L.FORM_SWEEP, L.FORM_AUTO)
+    b.close()
