@@ -420,6 +420,21 @@ int lbcg_batch_create(lbcg_sim *const *sims, int32_t n, const int32_t *tile, lbc
         return dev_err(e);
     }
     if (tuned) {
+        // The compact step is timed as later levels run it, on a compact state:
+        // a lattice that has none yet (its state is the pairs in buf[cur]) gets
+        // one in cbuf[cur], which it does not use until its own first compact
+        // step writes the other buffer.  The counter slot written is the one that
+        // step writes too.
+        for (int j = 0; j < n && b->compact; ++j) {
+            const lbcg_sim *s = sims[j];
+            if (s->compact) continue;
+            e = launch_step_compact(s->prec, s->g, s->md, s->buf[s->cur], true, s->cbuf[s->cur], s->ctr + s->cur,
+                                    s->ctr + (s->cur ^ 1), FusedShape{8, s->shape.zchunks, 64}, s->stream);
+            if (e != hipSuccess) {
+                destroy(b);
+                return dev_err(e);
+            }
+        }
         float best = 0;
         std::pair<int, int> pick = cand[0];
         for (const auto &c : cand) {

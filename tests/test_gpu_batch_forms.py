@@ -150,3 +150,39 @@ def test_timed_compact_batch_keeps_the_faster_form(L):  # noqa: F811
     b = L.Batch([s])
     assert b.step_form() == (L.FORM_SWEEP, L.FORM_AUTO)
     b.close()
+
+
+@pytest.mark.parametrize("prec", ["f32", "f16"])
+@pytest.mark.parametrize("before", [0, 1])
+def test_compact_batch_of_fresh_lattices_is_timed_on_their_state(L, prec, before):  # noqa: F811
+    # lattices that have not taken their first compact step, in device memory
+    # full of NaN: the timing works on compact states made from theirs (here
+    # seen in the handle's memory: two pair buffers, then the compact ones),
+    # and neither the states nor what follows change
+    import torch
+    w = _box((20, 17, 13), 1)
+    kw = dict(precision=prec, kernel=L.KERNEL_COMPACT)
+    n = L.Sim.from_workload(w, **kw).footprint
+    mem = torch.full((n + 256,), 255, dtype=torch.uint8, device="cuda")
+    ofs = -mem.data_ptr() % 256
+    stream = torch.cuda.current_stream().cuda_stream
+    s = L.Sim.from_workload(w, dev_buf=(mem.data_ptr() + ofs, n), stream=stream or None, **kw).step(before)
+    p = s.populations()
+    b = L.Batch([s])
+    s.synchronize()
+    E, dt = (4, torch.float32) if prec == "f32" else (2, torch.float16)
+    pitch = -(-w.nodes // 64) * 64
+    at = ofs + 2 * (-(-38 * pitch * E // 256) * 256)
+    got = 0
+    for k in range(2):
+        c = mem[at:at + 19 * pitch * E].view(dt).reshape(19, pitch)[:, :w.nodes]
+        got += bool(torch.isfinite(c).all())
+        at += -(-(pitch * (19 * E + (20 if E == 4 else 12))) // 256) * 256
+    print(f"compact states written by the timing {prec} after {before} steps: {got}", flush=True)
+    assert got == 2
+    assert np.array_equal(p, s.populations())
+    b.step(35)
+    b.close()
+    ref = L.Sim.from_workload(w, **kw).step(before + 35)
+    assert np.array_equal(s.populations(), ref.populations())
+    s.close()
