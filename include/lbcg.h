@@ -247,8 +247,9 @@ int lbcg_step(lbcg_sim *s, int64_t n);
  * Output pointers select the fields (NULL = skip).  Non-fluid nodes read 0.
  * Synchronizes.  Reads of 4 MiB and more, here and in lbcg_populations, go
  * through 16 MiB of pinned host memory and up to 7 host threads that the
- * library keeps per process while handles exist; one read at a time uses them,
- * others at that moment take plain copies. */
+ * library keeps per process, from the first 12 MiB of such reads on until the
+ * last handle goes; one read at a time uses them, others at that moment take
+ * plain copies. */
 int lbcg_fields(lbcg_sim *s, double *rhoR, double *rhoB, double *u, double *psi);
 
 /* Pre-collision populations f_i^k of S_t (the distributions of Eq. (1)) in

@@ -9,9 +9,13 @@
 // of 256^3 nodes (0.8 GB) 79 -> 23 ms (28 with 3 helpers), of 96^3 2.4 -> 1.1
 // ms, of 45 x 38 x 53 (4.4 MB) 0.26 -> 0.20 ms; 3 MB are even.
 //
-// The slots and helpers are one set per process, made at the first such read
-// and given back with the last handle; a read that finds them in use by another
-// thread, or cannot have them, takes the plain copies.  Helpers started for
+// The slots and helpers are one set per process, given back with the last
+// handle; a read that finds them in use by another thread, or cannot have them,
+// takes the plain copies.  To make and give them back costs 0.24 ms, what reads
+// of kFirstBytes in all gain: before that many bytes have been read since they
+// were last given back there are none, so that a program that holds one lattice
+// at a time and reads it once does not pay for them each time (45 x 38 x 53: 0.40
+// ms a read and lattice with them, 0.26 with plain copies).  Helpers started for
 // each read were slower where the program's own threads keep the CPUs busy: the
 // read then waits for each to be run once (16 boxes, each read followed by a
 // conversion on 16 threads: 52 ms in all against 12, and 18 with plain copies).
@@ -34,6 +38,7 @@ namespace {
 
 constexpr size_t kSlotBytes = size_t(8) << 20;
 constexpr size_t kMinBytes = size_t(4) << 20;
+constexpr size_t kFirstBytes = size_t(12) << 20;
 constexpr int kHelpers = 7;
 constexpr int64_t kPiece = 32768;  // doubles
 
@@ -155,6 +160,7 @@ struct Pool {
 
 std::mutex g_use;                   // held for the length of a read through the pool
 std::atomic<int64_t> g_handles{0};
+size_t g_plain = 0;                 // bytes of such reads since there were slots (under g_use)
 Pool *g_pool = nullptr;             // never freed at exit: its helpers may still wait
 
 hipError_t queue_chunk(lbcg_sim *s, RowsLaunch launch, const Read &rd, int64_t c, double *dev, double *host) {
@@ -231,11 +237,15 @@ void slots_release() {
     if (g_handles.load() != 0) return;
     delete g_pool;
     g_pool = nullptr;
+    g_plain = 0;
 }
 
-// The pool, for the thread that holds g_use; null if it cannot be had.
-static Pool *pool() {
+// The pool for a read of so many bytes, for the thread that holds g_use; null if
+// it does not pay yet or cannot be had.
+static Pool *pool(size_t bytes) {
     if (!g_pool) {
+        g_plain = bytes < kFirstBytes ? g_plain + bytes : kFirstBytes;
+        if (g_plain < kFirstBytes) return nullptr;
         g_pool = new (std::nothrow) Pool;
         if (g_pool && !g_pool->open()) {
             delete g_pool;
@@ -254,9 +264,10 @@ hipError_t read_rows(lbcg_sim *s, RowsLaunch launch, int rows, double *const *ds
             ++wanted;
             host = host && host_writable(dst[r]);
         }
-    if (host && size_t(wanted) * sizeof(double) * size_t(N) >= kMinBytes) {
+    const size_t bytes = size_t(wanted) * sizeof(double) * size_t(N);
+    if (host && bytes >= kMinBytes) {
         std::unique_lock<std::mutex> lock(g_use, std::try_to_lock);
-        Pool *p = lock.owns_lock() ? pool() : nullptr;
+        Pool *p = lock.owns_lock() ? pool(bytes) : nullptr;
         if (p) {
             try {
                 return read_slots(s, launch, rows, dst, *p);

@@ -1,0 +1,74 @@
+"""When the read slots and their helper threads exist, and that they disturb
+nothing: each case in a process of its own, which counts its threads and holds
+no other handles."""
+import os
+import subprocess
+import sys
+import textwrap
+
+import pytest
+
+pytestmark = pytest.mark.gpu
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+PRELUDE = """
+import ctypes as C, os, sys, threading
+import numpy as np, torch
+from paper_1711_02003_amd import lbcg as L, workloads as W
+assert torch.cuda.is_available()
+helpers = min(7, len(os.sched_getaffinity(0)) - 1)
+
+def threads():
+    return len(os.listdir("/proc/self/task"))
+
+def lattice(dims):
+    rng = np.random.default_rng(1)
+    rR, rB = W.colour_densities(rng.uniform(-0.9, 0.9, dims[::-1]))
+    return L.Sim("D3Q19", dims, 1.2, 0.7, 0.01, 0.7).init_fields(rR, rB).step(2)
+
+def read(s, out):
+    p = [C.cast(a, C.POINTER(C.c_double)) for a in out]
+    assert L.load_library().lbcg_fields(s._handle(), *p) == 0
+
+s = lattice((20, 20, 20))
+s.fields()
+s.close()
+base = threads()
+"""
+
+
+def _run(code):
+    if not __import__("torch").cuda.is_available():
+        pytest.skip("no GPU")
+    env = dict(os.environ, PYTHONPATH=ROOT, OMP_NUM_THREADS="1")
+    r = subprocess.run([sys.executable, "-u", "-c", PRELUDE + textwrap.dedent(code)], cwd=ROOT, env=env,
+                       capture_output=True, text=True, timeout=100)
+    print(r.stdout[-2000:], flush=True)
+    assert r.returncode == 0, r.stderr[-3000:]
+
+
+def test_one_lattice_at_a_time_reads_without_slots():
+    # 4.4 MB a read: a program that reads each lattice once does not pay for
+    # slots and threads; one that goes on reading gets them with the third read
+    _run("""
+        for _ in range(3):
+            s = lattice((45, 38, 53))
+            f = s.fields()
+            assert threads() == base, (threads(), base)
+            s.close()
+        s = lattice((45, 38, 53))
+        n = []
+        for _ in range(4):
+            g = s.fields()
+            n.append(threads() - base)
+            assert all(np.array_equal(f[k], g[k]) for k in f)
+        assert n == [0, 0, helpers, helpers], n
+        s.close()
+        assert threads() == base
+        # a large read pays for them at once
+        s = lattice((96, 96, 96))
+        s.fields()
+        assert threads() == base + helpers
+        s.close()
+        assert threads() == base
+    """)
