@@ -72,3 +72,24 @@ def test_one_lattice_at_a_time_reads_without_slots():
         s.close()
         assert threads() == base
     """)
+
+
+def test_pinned_destinations_are_written_by_the_device():
+    # no slots, no helpers; sizes around a slot's chunk of nodes, then the same
+    # reads into pageable memory, with and without slots
+    _run("""
+        for dims in ((61, 47, 43), (56, 56, 56), (83, 81, 79)):
+            s = lattice(dims)
+            n = s.N
+            pin = [torch.full((k * n,), float("nan"), dtype=torch.float64, pin_memory=True) for k in (1, 1, 3, 1)]
+            base = threads()  # torch has threads of its own for these
+            for _ in range(4):
+                read(s, [t.data_ptr() for t in pin])
+                assert threads() == base, (threads(), base)
+            for _ in range(4):
+                f = s.fields()
+                for k, t in zip(("rhoR", "rhoB", "u", "psi"), pin):
+                    assert np.array_equal(f[k].ravel(), t.numpy())
+            assert threads() == base + helpers
+            s.close()
+    """)
