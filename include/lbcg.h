@@ -290,7 +290,9 @@ int lbcg_synchronize(lbcg_sim *s);
  * stream while others compute on another (the served form). */
 int lbcg_set_stream(lbcg_sim *s, void *hip_stream);
 
-/* Release library-owned device memory and stream; never frees caller memory. */
+/* Waits for the handle's queued work, then releases library-owned device memory
+ * and stream; never frees caller memory.  Other threads' graph captures go on
+ * undisturbed. */
 void lbcg_destroy(lbcg_sim *s);
 
 /* Static description of an LBCG_* status code. */

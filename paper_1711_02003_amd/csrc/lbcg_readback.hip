@@ -126,11 +126,8 @@ struct Pool {
         }
     }
     bool open() {
-        // (relaxed: an allocation must not end a capture of another thread)
-        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-        (void)hipThreadExchangeStreamCaptureMode(&mode);
+        RelaxedCapture relaxed;
         const hipError_t e = hipHostMalloc(reinterpret_cast<void **>(&mem), 2 * kSlotBytes, hipHostMallocPortable);
-        (void)hipThreadExchangeStreamCaptureMode(&mode);
         if (e != hipSuccess) {
             (void)hipGetLastError();
             mem = nullptr;

@@ -1023,6 +1023,7 @@ int lbcg_tune(lbcg_sim *s, int32_t *rows, int32_t *zchunks) {
 
 void lbcg_destroy(lbcg_sim *s) {
     if (!s) return;
+    const RelaxedCapture relaxed;
     (void)hipStreamSynchronize(s->stream);
     release(s);
     slots_release();

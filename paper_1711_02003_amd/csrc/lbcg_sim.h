@@ -51,12 +51,26 @@ struct lbcg_sim {
 
 namespace lbcg {
 
+// Relaxed capture mode for the calling thread: its allocations, frees and waits
+// for streams that do not capture neither end a capture that another thread has
+// begun in global mode nor fail for it (a wait for a stream does both otherwise).
+class RelaxedCapture {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+
+public:
+    RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+    ~RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+    RelaxedCapture(const RelaxedCapture &) = delete;
+    RelaxedCapture &operator=(const RelaxedCapture &) = delete;
+};
+
 // Reads `rows` values per node to the host (lbcg_readback.hip): `launch` queues
 // the values of nodes [n0, n0 + cnt) into device memory as rows of cnt
 // doubles; row r of all nodes goes to dst[r] (null: not read).  Synchronizes.
 typedef hipError_t (*RowsLaunch)(lbcg_sim *s, int64_t n0, int64_t cnt, double *out);
 hipError_t read_rows(lbcg_sim *s, RowsLaunch launch, int rows, double *const *dst);
-// A handle comes and goes: the read slots are freed with the last one.
+// A handle comes and goes: the read slots are freed with the last one (call it
+// in relaxed capture mode).
 void slots_use();
 void slots_release();
 

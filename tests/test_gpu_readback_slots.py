@@ -93,3 +93,40 @@ def test_pinned_destinations_are_written_by_the_device():
             assert threads() == base + helpers
             s.close()
     """)
+
+
+def test_last_handle_goes_during_a_capture_of_another_thread():
+    # the slots are given back while this thread captures in global mode; the
+    # handle lives in memory and on a stream of the caller's, so that nothing
+    # else is freed with it
+    _run("""
+        side = torch.cuda.Stream()
+        x = torch.zeros(1000, device="cuda")
+        y = torch.empty_like(x)
+        for use in (1, 2):
+            rng = np.random.default_rng(1)
+            rR, rB = W.colour_densities(rng.uniform(-0.9, 0.9, (80, 80, 80)))
+            s = L.Sim("D3Q19", (80, 80, 80), 1.2, 0.7, 0.01, 0.7, stream=side.cuda_stream).init_fields(rR, rB).step(2)
+            f = s.fields()
+            assert threads() >= base + helpers
+            keep = s._buf
+            torch.cuda.synchronize()
+            done = []
+            def gone():
+                s.close()
+                done.append(threads())
+            g = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(g, capture_error_mode="global"):
+                y.copy_(x + 1)
+                t = threading.Thread(target=gone)
+                t.start()
+                t.join()
+                x.copy_(y)
+            assert len(done) == 1
+            for k in range(3):
+                x.fill_(10 * use + k)
+                g.replay()
+                torch.cuda.synchronize()
+                assert float(x[7]) == 10 * use + k + 1
+            del g, keep
+    """)
