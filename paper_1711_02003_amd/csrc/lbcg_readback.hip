@@ -198,19 +198,17 @@ hipError_t read_slots(lbcg_sim *s, RowsLaunch launch, int rows, double *const *d
     rd.per_row = (rd.chunk + kPiece - 1) / kPiece;
     rd.pieces = rd.per_row * rows;
     for (int k = 0; k < 2; ++k) rd.slot[k] = pool.mem + size_t(k) * kSlotBytes;
-    hipEvent_t ev[2] = {nullptr, nullptr};
-    hipError_t e = hipEventCreateWithFlags(&ev[0], hipEventDisableTiming);
-    if (e == hipSuccess) e = hipEventCreateWithFlags(&ev[1], hipEventDisableTiming);
     auto queue = [&](int64_t c) {
         const int k = int(c & 1);
-        const hipError_t q = queue_chunk(s, launch, rd, c, s->staging + k * half,
-                                         reinterpret_cast<double *>(pool.mem + size_t(k) * kSlotBytes));
-        return q == hipSuccess ? hipEventRecord(ev[k], s->stream) : q;
+        return queue_chunk(s, launch, rd, c, s->staging + k * half,
+                           reinterpret_cast<double *>(pool.mem + size_t(k) * kSlotBytes));
     };
-    if (e == hipSuccess) e = queue(0);
+    hipError_t e = queue(0);
     pool.set(shared);
     for (int64_t c = 0; c < rd.chunks && e == hipSuccess; ++c) {
-        e = hipEventSynchronize(ev[c & 1]);
+        // chunk c is the last work queued.  (No events: they belong to the device
+        // current in the calling thread, which need not be the handle's.)
+        e = hipStreamSynchronize(s->stream);
         if (e != hipSuccess) break;
         pool.arrive(rd, c);
         if (c + 1 < rd.chunks) {
@@ -226,8 +224,6 @@ hipError_t read_slots(lbcg_sim *s, RowsLaunch launch, int rows, double *const *d
     for (int64_t c = in < 2 ? 0 : in - 2; c < in; ++c) rd.drained(c);
     pool.set(nullptr);
     if (e != hipSuccess) (void)hipStreamSynchronize(s->stream);
-    for (hipEvent_t v : ev)
-        if (v) (void)hipEventDestroy(v);
     return e;
 }
 

@@ -130,3 +130,18 @@ def test_last_handle_goes_during_a_capture_of_another_thread():
                 assert float(x[7]) == 10 * use + k + 1
             del g, keep
     """)
+
+
+def test_read_with_another_device_current():
+    import torch
+    if torch.cuda.device_count() < 2:
+        pytest.skip("needs two GPUs: a read of a handle on the second while the first is current")
+    _run("""
+        with torch.cuda.device(1):
+            s = lattice((96, 96, 96))
+            want = s.fields()
+        for _ in range(2):
+            got = s.fields()  # device 0 is current
+            assert all(np.array_equal(got[k], want[k]) for k in want)
+        s.close()
+    """)
