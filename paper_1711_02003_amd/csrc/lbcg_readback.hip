@@ -24,6 +24,7 @@
 
 #include <atomic>
 #include <condition_variable>
+#include <cstdint>
 #include <cstring>
 #include <memory>
 #include <mutex>
@@ -53,9 +54,19 @@ bool pageable(const void *p) {
     }
     return at.type == hipMemoryTypeUnregistered;
 }
-bool pageable(int rows, double *const *dst) {
-    for (int r = 0; r < rows; ++r)
-        if (dst[r] && !pageable(dst[r])) return false;
+// Whether the rows of N doubles can go through the slots: all pageable, and none
+// over another (the threads copy rows at the same time; in the plain copies the
+// last row stands).
+bool for_slots(int rows, double *const *dst, int64_t N) {
+    for (int r = 0; r < rows; ++r) {
+        if (!dst[r]) continue;
+        const uintptr_t a = reinterpret_cast<uintptr_t>(dst[r]), len = sizeof(double) * uintptr_t(N);
+        for (int q = 0; q < r; ++q) {
+            const uintptr_t b = reinterpret_cast<uintptr_t>(dst[q]);
+            if (dst[q] && a < b + len && b < a + len) return false;
+        }
+        if (!pageable(dst[r])) return false;
+    }
     return true;
 }
 
@@ -260,7 +271,7 @@ hipError_t read_rows(lbcg_sim *s, RowsLaunch launch, int rows, double *const *ds
     int64_t wanted = 0;
     for (int r = 0; r < rows; ++r) wanted += dst[r] ? 1 : 0;
     const size_t bytes = size_t(wanted) * sizeof(double) * size_t(N);
-    if (bytes >= kMinBytes && pageable(rows, dst)) {
+    if (bytes >= kMinBytes && for_slots(rows, dst, N)) {
         std::unique_lock<std::mutex> lock(g_use, std::try_to_lock);
         Pool *p = lock.owns_lock() ? pool(bytes) : nullptr;
         if (p) {

@@ -145,3 +145,20 @@ def test_read_with_another_device_current():
             assert all(np.array_equal(got[k], want[k]) for k in want)
         s.close()
     """)
+
+
+def test_overlapping_destinations_hold_the_last_row():
+    # one place for several rows: it holds the last of them, as with plain copies
+    _run("""
+        s = lattice((96, 96, 96))
+        n = s.N
+        f = [s.fields() for _ in range(2)][1]  # the slots exist
+        buf = np.empty(3 * n)
+        for _ in range(30):
+            buf[:] = np.nan
+            read(s, [buf[:n].ctypes.data, None, None, buf[:n].ctypes.data])
+            assert np.array_equal(buf[:n], f["psi"].ravel())
+            read(s, [buf[:n].ctypes.data, buf[n:2 * n].ctypes.data, buf.ctypes.data, buf[2 * n:].ctypes.data])
+            assert np.array_equal(buf[:2 * n], f["u"].reshape(-1)[:2 * n])
+            assert np.array_equal(buf[2 * n:], f["psi"].ravel())
+    """)
