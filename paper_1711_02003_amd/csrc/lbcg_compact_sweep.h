@@ -131,13 +131,6 @@ __device__ __forceinline__ void store_h1(__amdgpu_buffer_rsrc_t r, uint32_t voff
 // entries {M with flag, V_axis} and R_d.
 template <typename S>
 struct CStore;
-// One node's new state as stored.
-template <typename S>
-struct CStored {
-    typename CStore<S>::Raw t[D3Q19::Q];
-    typename CStore<S>::RawA a;
-    typename CStore<S>::RawB b;
-};
 template <>
 struct CStore<float> {
     static constexpr uint32_t E = 4, kRecA = 16, kRecB = 4;
@@ -156,10 +149,6 @@ struct CStore<float> {
     }
     __device__ static __forceinline__ f4 entry(RawA v, RawB) { return v; }
     __device__ static __forceinline__ float ratio(RawB v) { return __builtin_bit_cast(float, v); }
-    // The stored form, and its store: store() in two parts.
-    __device__ static __forceinline__ CStored<float> encode(const CompactOut<D3Q19, float> &o, uint32_t, uint32_t);
-    __device__ static __forceinline__ void put(__amdgpu_buffer_rsrc_t rout, uint32_t own, uint32_t zcol, uint32_t pitch,
-                                               const CStored<float> &st);
     // Compact output of the node at byte column `own` (E bytes per node) of
     // the plane that starts at node zcol.
     __device__ static __forceinline__ void store(__amdgpu_buffer_rsrc_t rout, uint32_t own, uint32_t zcol, uint32_t pitch,
@@ -210,10 +199,6 @@ struct CStore<_Float16> {
         const uint32_t t = Codec<_Float16>::sr_bits<13>(__float_as_uint(x), r);
         return __builtin_bit_cast(uint16_t, _Float16(__uint_as_float(t)));
     }
-    __device__ static __forceinline__ CStored<_Float16> encode(const CompactOut<D3Q19, float> &o, uint32_t step,
-                                                               uint32_t node);
-    __device__ static __forceinline__ void put(__amdgpu_buffer_rsrc_t rout, uint32_t own, uint32_t zcol, uint32_t pitch,
-                                               const CStored<_Float16> &st);
     // Random bits: 13 per value, two values per 32-bit draw (bits 0-12 and
     // 16-28): draws 0-9 for the 19 totals and R_d, 10-11 for V_axis.
     __device__ static __forceinline__ void store(__amdgpu_buffer_rsrc_t rout, uint32_t own, uint32_t zcol, uint32_t pitch,
@@ -241,51 +226,6 @@ struct CStore<_Float16> {
         store_u1(rout, own * (kRecB / E), ob, rb);
     }
 };
-
-__device__ __forceinline__ CStored<float> CStore<float>::encode(const CompactOut<D3Q19, float> &o, uint32_t, uint32_t) {
-    CStored<float> st;
-#pragma unroll
-    for (int i = 0; i < D3Q19::Q; ++i) st.t[i] = __builtin_bit_cast(uint32_t, o.df[i]);
-    st.a = f4{Codec<float>::enc_col<float>(o.M, o.redmaj), o.Va[0], o.Va[1], o.Va[2]};
-    st.b = __builtin_bit_cast(uint32_t, o.Rd);
-    return st;
-}
-__device__ __forceinline__ void CStore<float>::put(__amdgpu_buffer_rsrc_t rout, uint32_t own, uint32_t zcol,
-                                                   uint32_t pitch, const CStored<float> &st) {
-    const uint32_t cs = pitch * E, zoff = zcol * E;
-#pragma unroll
-    for (int i = 0; i < D3Q19::Q; ++i) store_u1(rout, own, uint32_t(i) * cs + zoff, st.t[i]);
-    const uint32_t ra = uint32_t(D3Q19::Q) * cs + zcol * kRecA,
-                   rb = uint32_t(D3Q19::Q) * cs + pitch * kRecA + zcol * kRecB;
-    const f2 a01 = {st.a[0], st.a[1]}, a23 = {st.a[2], st.a[3]};
-    store_u2(rout, own * (kRecA / E), ra, __builtin_bit_cast(u2, a01));
-    store_u2(rout, own * (kRecA / E), ra + 8u, __builtin_bit_cast(u2, a23));
-    store_u1(rout, own * (kRecB / E), rb, st.b);
-}
-__device__ __forceinline__ CStored<_Float16> CStore<_Float16>::encode(const CompactOut<D3Q19, float> &o, uint32_t step,
-                                                                      uint32_t node) {
-    CStored<_Float16> st;
-    Dither dz(step, node);
-    uint32_t w = 0;
-#pragma unroll
-    for (int i = 0; i < D3Q19::Q; ++i) {
-        if ((i & 1) == 0) w = dz.next();
-        st.t[i] = __builtin_bit_cast(uint16_t, Codec<_Float16>::enc_df_sr<D3Q19, float>(o.df[i], i, (i & 1) ? w >> 16 : w));
-    }
-    const uint32_t rd = sr(o.Rd, w >> 16);
-    w = dz.next();
-    st.a = u2{__float_as_uint(Codec<float>::enc_col<float>(o.M, o.redmaj)), sr(o.Va[0], w) | (sr(o.Va[1], w >> 16) << 16)};
-    st.b = sr(o.Va[2], dz.next()) | (rd << 16);
-    return st;
-}
-__device__ __forceinline__ void CStore<_Float16>::put(__amdgpu_buffer_rsrc_t rout, uint32_t own, uint32_t zcol,
-                                                      uint32_t pitch, const CStored<_Float16> &st) {
-    const uint32_t cs = pitch * E, zoff = zcol * E;
-#pragma unroll
-    for (int i = 0; i < D3Q19::Q; ++i) store_h1(rout, own, uint32_t(i) * cs + zoff, st.t[i]);
-    store_u2(rout, own * (kRecA / E), uint32_t(D3Q19::Q) * cs + zcol * kRecA, st.a);
-    store_u1(rout, own * (kRecB / E), uint32_t(D3Q19::Q) * cs + pitch * kRecA + zcol * kRecB, st.b);
-}
 
 __device__ __forceinline__ void c_lds_barrier() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");

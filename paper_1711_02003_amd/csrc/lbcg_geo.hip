@@ -534,7 +534,7 @@ __global__ void __launch_bounds__(kGeoBlock) k_cgeo_collide(CGeoArgs ca) {
     CompactOut<L, float> o;
     split_collide(a.mo, mv, F, o);
     const __amdgpu_buffer_rsrc_t rout = state_rsrc(static_cast<uint8_t *>(a.out), c_bytes<S>() * a.pitch);
-    St::put(rout, h.n * St::E, 0u, a.pitch, St::encode(o, step, h.n));
+    St::store(rout, h.n * St::E, 0u, a.pitch, o, step);
 }
 
 // Inlet and outlet values from the stored totals and record of the node that

@@ -967,9 +967,9 @@ int lbcg_tune(lbcg_sim *s, int32_t *rows, int32_t *zchunks) {
                        : launch_fused(s, in, out, ctr_in, ctr_out, c);
         };
         // Two passes over the candidates, each keeping its faster time: in a
-        // single pass the first candidates ran while the clocks were still
-        // rising, and a 7 % faster D2Q9 shape lost to a slower one about
-        // half the time.
+        // single pass the first candidates run while the clocks are still
+        // rising, and a shape 7 % faster lost to a slower one about half the
+        // time.
         std::vector<float> best_ms(cand.size(), 0.0f);
         hipError_t e = hipSuccess;
         for (int pass = 0; pass < 2 && e == hipSuccess; ++pass) {

@@ -132,11 +132,9 @@ struct Around {
         return UZ ? c : c + zp[1 + dz];
     }
     __device__ __forceinline__ uint32_t base(int dz) const { return UZ ? zp[1 + dz] : 0u; }
-    // of the upstream node x - c_i, and the node itself
+    // of the upstream node x - c_i
     __device__ __forceinline__ uint32_t vo(int i) const { return lane(-D3Q19::cx[i], -D3Q19::cy[i], -D3Q19::cz[i]); }
     __device__ __forceinline__ uint32_t so(int i) const { return base(-D3Q19::cz[i]); }
-    __device__ __forceinline__ uint32_t own() const { return lane(0, 0, 0); }
-    __device__ __forceinline__ uint32_t own_base() const { return base(0); }
 };
 
 // The 19 pairs that a node pulls, plain loads all (boundary values lie in the

@@ -14,7 +14,7 @@
 // Threads are numbered along a plane (x fastest, rows run together), so every
 // lane works whatever the width, and the grid has a thread per node.  The
 // price is the moments written and read back, 104 bytes per node, and a
-// second launch, so large lattices stay on the sweeps (split_preferred).
+// second launch, so large lattices stay on the sweeps (split_faster).
 // Every value is formed by the sweeps' expressions in their order: the
 // results are bitwise the sweeps'.
 //
