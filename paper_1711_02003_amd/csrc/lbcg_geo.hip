@@ -20,7 +20,7 @@
 // 50 (FP16) bytes of state per fluid node instead of 2 x 152 or 2 x 76.
 //
 // Work: thread k takes entry k of the list of fluid nodes {node, link word},
-// built once per lattice in node order.  Blocks of 64 x 4 nodes (with a list
+// built once per lattice.  Blocks of 64 x 4 nodes (with a list
 // of those that hold fluid) left a third of the lanes idle on step-emulsifier
 // channels and read the link words of solid nodes: 412 us a level for eight
 // of them (FP32) against 370.  With the nodes that have inlet or outlet links
@@ -89,21 +89,39 @@ __device__ __forceinline__ bool has_io_link(uint32_t lk) {
     return (lk & kLinkBits) && ((lk & kLinkMixed) || !is_wall(link_code(lk)));
 }
 
-// List builder.  Block b goes through nodes [b kChunk, (b + 1) kChunk):
+// Order of the lists: number t of a lattice's N nodes.  Rows one after another,
+// except where every row starts on a 64-node boundary: there by 64 x 8 nodes, so
+// that a block reads its neighbours' lines (and on the compact state the records,
+// which serve 19 receivers) for eight rows at once.  Junction 512 x 128 x 64 FP32
+// compact 112 -> 107 us a step (110 with blocks of 64 x 4 nodes before there was a
+// list), 256 x 64 x 32 FP16 compact 28 -> 26; on rows that start anywhere a wave
+// then reaches over two rows that share no line (channel of 386 x 130 x 66 nodes
+// 125 -> 153 us, duct of 300 x 40 x 30 40 -> 42).
+constexpr uint32_t kListX = 64, kListY = 8;
+__device__ __forceinline__ uint32_t listed_node(uint32_t t, uint32_t nx, uint32_t ny) {
+    if (nx % kListX != 0) return t;
+    const uint32_t plane = nx * ny, z = t / plane, p = t - z * plane;
+    const uint32_t band = p / (kListY * nx), h = min(kListY, ny - kListY * band);  // rows of the band
+    const uint32_t q = p - band * kListY * nx, b = q / (kListX * h), r = q - b * kListX * h;
+    return z * plane + (kListY * band + r / kListX) * nx + kListX * b + r % kListX;
+}
+
+// List builder.  Block b goes through numbers [b kChunk, (b + 1) kChunk):
 // without lists it counts its fluid nodes and those with inlet or outlet
 // links; with them it writes their entries from the offsets that k_geo_scan
 // put in place of the counts.
-__global__ void __launch_bounds__(kGeoBlock) k_geo_list(const uint32_t *__restrict__ links, uint32_t N,
-                                                       uint32_t *__restrict__ counts, uint32_t *__restrict__ list,
-                                                       uint32_t *__restrict__ io) {
+__global__ void __launch_bounds__(kGeoBlock) k_geo_list(const uint32_t *__restrict__ links, uint32_t N, uint32_t nx,
+                                                       uint32_t ny, uint32_t *__restrict__ counts,
+                                                       uint32_t *__restrict__ list, uint32_t *__restrict__ io) {
     __shared__ uint32_t wc[2][kGeoBlock / 64];
     const int w = int(threadIdx.x / 64);
     uint32_t at[2] = {0, 0};
     if (list)
         for (int c = 0; c < 2; ++c) at[c] = counts[2 * blockIdx.x + c];
     for (uint32_t k = 0; k < kChunk; k += kGeoBlock) {
-        const uint32_t n = blockIdx.x * kChunk + k + threadIdx.x;
-        const uint32_t lk = n < N ? links[n] : 0u;
+        const uint32_t t = blockIdx.x * kChunk + k + threadIdx.x;
+        const uint32_t n = t < N ? listed_node(t, nx, ny) : 0u;
+        const uint32_t lk = t < N ? links[n] : 0u;
         const bool mine[2] = {(lk & kLinkFluid) != 0u, (lk & kLinkFluid) && has_io_link(lk)};
         uint32_t e[2];
         __syncthreads();  // the counts of the pass before have been read
@@ -655,13 +673,13 @@ hipError_t split_prepare(const Geo &g, void *scratch, SplitPlan &sp, hipStream_t
     sp = SplitPlan{};
     if (!g.links || !g.mask || !scratch) return hipErrorInvalidValue;
     const ScratchMap m = scratch_map(scratch, g.pitch);
-    const uint32_t N = uint32_t(g.N), chunks = uint32_t((g.N + kChunk - 1) / kChunk);
+    const uint32_t N = uint32_t(g.N), nx = uint32_t(g.nx), ny = uint32_t(g.ny), chunks = uint32_t((g.N + kChunk - 1) / kChunk);
     uint32_t *none = nullptr;
     hipLaunchKernelGGL(k_geo_solid_psi, dim3(unsigned((g.N + kGeoBlock - 1) / kGeoBlock)), dim3(kGeoBlock), 0, s, g,
                        m.psi);
-    hipLaunchKernelGGL(k_geo_list, dim3(chunks), dim3(kGeoBlock), 0, s, g.links, N, m.counts, none, none);
+    hipLaunchKernelGGL(k_geo_list, dim3(chunks), dim3(kGeoBlock), 0, s, g.links, N, nx, ny, m.counts, none, none);
     hipLaunchKernelGGL(k_geo_scan, dim3(1), dim3(kScanThreads), 0, s, m.counts, chunks, m.totals);
-    hipLaunchKernelGGL(k_geo_list, dim3(chunks), dim3(kGeoBlock), 0, s, g.links, N, m.counts, m.list, m.io);
+    hipLaunchKernelGGL(k_geo_list, dim3(chunks), dim3(kGeoBlock), 0, s, g.links, N, nx, ny, m.counts, m.list, m.io);
     hipError_t e = hipGetLastError();
     uint32_t c[2] = {0, 0};
     if (e == hipSuccess) e = hipMemcpyAsync(c, m.totals, sizeof(c), hipMemcpyDeviceToHost, s);
