@@ -86,7 +86,9 @@ def _first_run(ks, timed):
     """The last `timed` dispatches of the first run of at least `timed`
     consecutive dispatches with one launch shape: the headline's warm-up and
     timed steps, after the tuner's trials (runs of 6 per shape) and before
-    the forms that later run the same kernel on other lattices."""
+    the forms that later run the same kernel on other lattices.  None if there
+    is no such run: then the kernel's dispatches are trials, and no timed
+    region ran it."""
     runs, cur = [], []
     for r in ks:
         key = (r["Grid_Size_X"], r["Workgroup_Size_X"])
@@ -99,7 +101,7 @@ def _first_run(ks, timed):
     for run in runs:
         if len(run) >= timed:
             return run[-timed:]
-    return ks[-timed:]
+    return None
 
 
 def trace_summary(trace_csv, out_md, kernel_sub, timed, command, region="last"):
@@ -120,7 +122,9 @@ def trace_summary(trace_csv, out_md, kernel_sub, timed, command, region="last"):
     for pat in KERNELS[kernel_sub][2]:
         ks = _matches(rows, pat)
         ks.sort(key=lambda r: int(r["Start_Timestamp"]))
-        tail = _first_run(ks, timed) if region == "first" else ks[-timed:]
+        tail = _first_run(ks, timed) if region == "first" else ks[-timed:] if len(ks) >= timed else None
+        if tail is None:
+            raise SystemExit(f"no timed region of {timed} dispatches matches {pat}: {len(ks)} dispatches in shorter runs")
         d = [(int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) / 1e3 for r in tail]
         span = (int(tail[-1]["End_Timestamp"]) - int(tail[0]["Start_Timestamp"])) / 1e3
         grid = {(r["Grid_Size_X"], r["Workgroup_Size_X"]) for r in tail}
@@ -149,6 +153,8 @@ def _kernel_values(counter_csv, counter, kernel_sub, timed):
     for pat in KERNELS[kernel_sub][2]:
         ks = _matches(rows, pat)
         ks.sort(key=lambda r: int(r["Dispatch_Id"]))
+        if len(ks) < timed:
+            raise SystemExit(f"{len(ks)} dispatches match {pat}, fewer than the {timed} timed")
         vals = [float(r["Counter_Value"]) for r in ks[-timed:]]
         total += sum(vals) / len(vals)
         n = len(vals) if n is None else min(n, len(vals))
@@ -192,6 +198,8 @@ def traffic_summary(fetch_csv, write_csv, kernel_sub, timed, nodes, out_txt, com
 FORM_KERNELS = [("D3Q19 256³ droplets, FP32 pairs", r"k_step_fused<float, float, \d, false, false>"),
                 ("D3Q19 256³ droplets, FP16 compact", r"k_step_compactILb0ELi\d+EDF16_"),
                 ("D3Q19 256³ droplets, FP16 pairs", r"k_step_fusedIDF16_fLi\dELb0ELb0E"),
+                ("D3Q19 256³ droplets, FP16 pairs, split: moments", r"k_split_momentsIDF16_Lb0ELb0E"),
+                ("D3Q19 256³ droplets, FP16 pairs, split: collision", r"k_split_collideIDF16_Lb0E"),
                 ("D2Q9 4096² droplets, FP32 compact", r"k_tile2d_compact<"),
                 ("D2Q9 4096² droplets, FP32", r"k_tile2d<float, float, false, false, false"),
                 ("D2Q9 junction 8192×2048, FP32", r"k_tile2d<float, float, true, false, false"),
@@ -206,27 +214,32 @@ FORM_KERNELS = [("D3Q19 256³ droplets, FP32 pairs", r"k_step_fused<float, float
                 ("D3Q19 junction 512×128×64, FP16 split: moments", r"k_geo_momentsIDF16_Lb0E"),
                 ("D3Q19 junction 512×128×64, FP16 split: collision", r"k_geo_collideIDF16_"),
                 ("D3Q19 64 boxes batched, FP32 pairs", r"k_step_fused_batch<float, float, \d, false>"),
+                ("D3Q19 64 boxes batched, FP32 pairs, split: moments", r"k_split_moments_batch<float, false>"),
+                ("D3Q19 64 boxes batched, FP32 pairs, split: collision", r"k_split_collide_batch<float, false>"),
                 ("D3Q19 64 boxes batched, FP32 compact", r"k_step_compact_batch")]
 
 
 def forms_summary(trace_csv, out_md, timed, command):
-    """Per benchmark form, the last `timed` dispatches of its fused kernel
-    (each form's timed region comes after its warm-up and tuning)."""
+    """Per benchmark form, the last `timed` dispatches of its kernels (each
+    form's timed region comes after its warm-up and tuning).  A form may be
+    timed on one of several steps, as the tuner picks: the rows are those of
+    the kernels that a timed region ran."""
     rows = list(csv.DictReader(open(trace_csv)))
     lines = ["# rocprofv3 kernel trace: benchmark forms (fused sweeps)", "",
              f"Command: `{command}`", "",
              f"Each form times {timed} steps after its warm-up (and, for the fused sweeps, after the tuner's "
              f"trial launches); the rows below take, per kernel, the last {timed} dispatches of its first run "
              f"of at least {timed} consecutive same-shape dispatches, i.e. that form's timed region (later "
-             "forms run some of these kernels again on other lattices).", "",
+             "forms run some of these kernels again on other lattices); kernels that ran only as the tuner's "
+             "trials have no row.", "",
              "| form | kernel | dispatches in run | avg us (timed) | min us | max us | "
              "first start to last end, per dispatch us |",
              "|---|---|---|---|---|---|---|"]
     for form, pat in FORM_KERNELS:
         ks = sorted(_matches(rows, pat), key=lambda r: int(r["Start_Timestamp"]))
-        if not ks:
-            continue
         tail = _first_run(ks, timed)
+        if tail is None:  # no timed region ran this kernel
+            continue
         d = [(int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) / 1e3 for r in tail]
         span = (int(tail[-1]["End_Timestamp"]) - int(tail[0]["Start_Timestamp"])) / 1e3
         lines.append(f"| {form} | `{pat}` | {len(ks)} | {sum(d) / len(d):.1f} | "
