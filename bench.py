@@ -192,6 +192,14 @@ def time_sim(torch, sim, stream, steps, warmup):
     return e0.elapsed_time(e1)
 
 
+STEP_NAMES = ("", "sweep", "split", "tile", "two passes")  # by lbcg.FORM_*
+
+
+def shape_info(info):
+    """Launch shape of a handle with the name of the step that runs."""
+    return {**{k: v for k, v in info.items() if k in ("rows", "zchunks", "tile_width")}, "step": STEP_NAMES[info["form"]]}
+
+
 def pair_f32_form(torch, lbcg, W, size, steps=200, warmup=10):
     w = W.droplets_27(L=size, seed=2)
     stream = torch.cuda.Stream()
@@ -204,8 +212,8 @@ def pair_f32_form(torch, lbcg, W, size, steps=200, warmup=10):
     gbs = 304 * w.fluid_nodes * steps / (ms / 1e3) / 1e9
     return {"workload": w.name, "storage": "f32 pairs", "mlups": round(mlups, 1),
             "ms_per_step": round(ms / steps, 4), "achieved_gbs": round(gbs, 1),
-            "frac": round(gbs / HBM_PEAK_GBS, 4), "bytes_per_node": 304, "rows": shape["rows"],
-            "zchunks": shape["zchunks"], "steps": steps}
+            "frac": round(gbs / HBM_PEAK_GBS, 4), "bytes_per_node": 304, "step": STEP_NAMES[shape["form"]],
+            "rows": shape["rows"], "zchunks": shape["zchunks"], "steps": steps}
 
 
 def f16_form(torch, lbcg, W, size, steps=200, warmup=10):
@@ -225,7 +233,7 @@ def f16_form(torch, lbcg, W, size, steps=200, warmup=10):
         gbs = bpn * w.fluid_nodes * steps / (ms / 1e3) / 1e9
         out[name] = {"mlups": round(mlups, 1), "ms_per_step": round(ms / steps, 4),
                      "achieved_gbs": round(gbs, 1), "frac": round(gbs / HBM_PEAK_GBS, 4), "bytes_per_node": bpn,
-                     "shape": shape, "steps": steps}
+                     "shape": shape_info(shape), "steps": steps}
     return out
 
 
@@ -291,7 +299,7 @@ def focusing_form(torch, lbcg, W, steps=200, warmup=10, tune=True):
                      "lattice_mlups": round(w.nodes * steps / (ms / 1e3) / 1e6, 1),
                      "ms_per_step": round(ms / steps, 4),
                      "frac": round((2 * 38 * elem + 4) * w.fluid_nodes * steps / (ms / 1e3) / 1e9 / HBM_PEAK_GBS, 4),
-                     "rows": shape["rows"], "zchunks": shape["zchunks"]}
+                     "step": STEP_NAMES[shape["form"]], "rows": shape["rows"], "zchunks": shape["zchunks"]}
         if prec == "f32" and shape["rows"] == 0:
             out[prec]["traffic"] = read_traffic("geo_split")
     # the compact state on the split step: 2 x 96 (FP32) or 2 x 50 (FP16)
@@ -354,7 +362,8 @@ def batched_form(torch, lbcg, W, steps=200, warmup=10, compact=False, precision=
             "state": "compact" if compact else "pairs", "storage": precision, "bytes_per_node": bpn,
             "steps": steps, "batched_mlups": round(mb, 1), "plain_mlups": round(mp, 1),
             "speedup": round(mb / mp, 3), "frac": round(mb * bpn / 1e3 / HBM_PEAK_GBS, 4),
-            "rows": info["rows"], "zplanes": info["zplanes"], "blocks": info["blocks"]}
+            "step": STEP_NAMES[info["forms"][0]], "rows": info["rows"], "zplanes": info["zplanes"],
+            "blocks": info["blocks"]}
 
 
 def served_form(torch, lbcg, W, n=64, steps_scale=0.1, loads=(0.8, 1.5), capacity=0.0):
@@ -491,7 +500,9 @@ def main():
     bytes_node = (2 * (19 * 4 + 20) if elem == 4 else 2 * (19 * 2 + 12)) if compact else 2 * 2 * 19 * elem
     mlups = N * args.steps / (ms / 1e3) / 1e6
     achieved = bytes_node * N / (ms_step / 1e3) / 1e9
-    traffic = read_traffic(kname) if args.precision == "f32" and args.size == 256 else None
+    # the counters were taken on the sweep
+    swept = args.precision == "f32" and args.size == 256 and info["form"] == lbcg.FORM_SWEEP
+    traffic = read_traffic(kname) if swept else None
     out = {
         "metric": "two-component MLUPS, D3Q19 regularized colour-gradient step",
         "value": round(mlups, 1),
@@ -508,7 +519,7 @@ def main():
         "config": {"workload": w.name, "lattice": "D3Q19", "dims": list(w.dims),
                    "droplets": 27, "tau_R": w.tau_R, "tau_B": w.tau_B, "A": w.A, "beta": w.beta,
                    "storage": args.precision, "kernel": "fused compact" if compact else "fused",
-                   "rows": info["rows"], "zchunks": info["zchunks"], "tile_width": info["tile_width"]},
+                   **shape_info(info)},
         "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
                      "traffic": traffic, "bytes_per_node": bytes_node},
