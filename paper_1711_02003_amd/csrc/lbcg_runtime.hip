@@ -198,7 +198,10 @@ int64_t sweep_planes(const lbcg_sim *s, const FusedShape &sh, int64_t resident, 
 // chunks as fill the device once, the rule before, left a second round of
 // blocks half empty: 210 x 150 x 131 FP32 548 us per step with 4 chunks, 304
 // blocks on 256 CUs, against 398 with 3, and short columns of planes unsplit:
-// 45 x 38 x 53 62 us with 6 chunks, 20 with 27.)
+// 45 x 38 x 53 62 us with 6 chunks, 20 with 27.  With geometry and plain BGK, the
+// rule before -> this one: mostly fluid ducts of 64 x 32 x 32 142 -> 23 us, 200 x
+// 100 x 80 378 -> 246, 256 x 128 x 128 499 -> 455, FP16 464 -> 467; BGK 45 x 38 x 53
+// 83 -> 31, 210 x 150 x 131 759 -> 539, 200 x 100 x 80 with geometry 602 -> 411.)
 int64_t best_zchunks(const lbcg_sim *s, const FusedShape &sh, int64_t resident) {
     int64_t best = 1, cost = 0;
     for (int64_t zc = 1; zc <= s->g.nz && zc <= 4096; ++zc) {
